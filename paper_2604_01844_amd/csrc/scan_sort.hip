@@ -50,16 +50,34 @@ __device__ __forceinline__ T block_exclusive_scan(T v, T *wsum, T &total) {
   return base + x - v;
 }
 
+// Where a scan takes its values from: the array it also writes to, or the
+// quantised weights of a float array, floor(v * 2^24 / max) (plain FP32, as
+// stated at exclusive_scan_quantized), which are then never stored by
+// themselves.
 template <typename T>
-__global__ __launch_bounds__(kThreads) void scan_reduce_kernel(const T *__restrict__ data, uint64_t n,
-                                                               T *__restrict__ partial) {
+struct ScanArray {
+  const T *data;
+  __device__ __forceinline__ T operator()(uint64_t i) const { return data[i]; }
+};
+
+struct ScanQuantized {
+  const float *v, *vmax;
+  __device__ __forceinline__ uint64_t operator()(uint64_t i) const {
+#pragma clang fp contract(off)
+    const float scale = 16777216.f / vmax[0];
+    return static_cast<uint64_t>(floorf(v[i] * scale));
+  }
+};
+
+template <typename T, typename Load>
+__global__ __launch_bounds__(kThreads) void scan_reduce_kernel(Load load, uint64_t n, T *__restrict__ partial) {
   __shared__ T wsum[kWaves];
   const uint64_t base = uint64_t(blockIdx.x) * kTile;
   T s = 0;
 #pragma unroll
   for (int j = 0; j < kItems; ++j) {
     uint64_t idx = base + uint64_t(j) * kThreads + threadIdx.x;
-    s += (idx < n) ? data[idx] : T(0);
+    s += (idx < n) ? load(idx) : T(0);
   }
   T total;
   block_exclusive_scan(s, wsum, total);
@@ -98,8 +116,8 @@ __device__ __forceinline__ void write_count(const CountOut &co, unsigned long lo
 // up every tile's sum in 64 bits (a scanned offset table gives them as
 // differences of neighbours, exact while one tile's sum fits 32 bits), so
 // a 32-bit wrap of the offsets is detected.
-template <typename T>
-__global__ __launch_bounds__(kThreads) void scan_apply_kernel(T *__restrict__ data, uint64_t n,
+template <typename T, typename Load>
+__global__ __launch_bounds__(kThreads) void scan_apply_kernel(Load load, T *data, uint64_t n,
                                                               const T *__restrict__ partial,
                                                               uint32_t n_tiles, int self_prefix, CountOut co) {
   __shared__ T tile[kTile + kTile / 32];
@@ -134,7 +152,7 @@ __global__ __launch_bounds__(kThreads) void scan_apply_kernel(T *__restrict__ da
   for (int j = 0; j < kItems; ++j) {
     int li = j * kThreads + threadIdx.x;
     uint64_t idx = base + li;
-    tile[pad(li)] = (idx < n) ? data[idx] : T(0);
+    tile[pad(li)] = (idx < n) ? load(idx) : T(0);
   }
   __syncthreads();
   T v[kItems];
@@ -347,8 +365,8 @@ uint64_t scan_scratch_words(uint64_t n) {
   return words + 64;
 }
 
-template <typename T>
-static int exclusive_scan(T *data, uint64_t n, T *scratch, hipStream_t s, CountOut co = CountOut{}) {
+template <typename T, typename Load>
+static int exclusive_scan_of(Load load, T *data, uint64_t n, T *scratch, hipStream_t s, CountOut co = CountOut{}) {
   if (n == 0) {
     // total of an empty array (a kernel, not a memset node, so the call can be captured)
     set_zero_kernel<T><<<1, 1, 0, s>>>(data, co);
@@ -357,25 +375,30 @@ static int exclusive_scan(T *data, uint64_t n, T *scratch, hipStream_t s, CountO
   }
   const uint64_t tiles = (n + kTile - 1) / kTile;
   if (tiles == 1) {
-    scan_apply_kernel<T><<<1, kThreads, 0, s>>>(data, n, nullptr, 1, 0, co);
+    scan_apply_kernel<T><<<1, kThreads, 0, s>>>(load, data, n, nullptr, 1, 0, co);
     FGS_LAUNCH_CHECK("scan_apply_kernel");
     return FGS_OK;
   }
   if (tiles > 0xffffffffull) return fail(FGS_E_UNSUPPORTED, "scan: too many elements");
   T *partial = scratch;
   T *rest = scratch + align_up((tiles + 1) * sizeof(T)) / sizeof(T);
-  scan_reduce_kernel<T><<<unsigned(tiles), kThreads, 0, s>>>(data, n, partial);
+  scan_reduce_kernel<T><<<unsigned(tiles), kThreads, 0, s>>>(load, n, partial);
   FGS_LAUNCH_CHECK("scan_reduce_kernel");
   // few tiles: each block adds up the sums before it (two launches in all);
   // many: the sums are scanned first
   const int self_prefix = tiles <= kSelfPrefixTiles ? 1 : 0;
   if (!self_prefix) {
-    int st = exclusive_scan<T>(partial, tiles, rest, s);
+    int st = exclusive_scan_of<T>(ScanArray<T>{partial}, partial, tiles, rest, s);
     if (st != FGS_OK) return st;
   }
-  scan_apply_kernel<T><<<unsigned(tiles), kThreads, 0, s>>>(data, n, partial, unsigned(tiles), self_prefix, co);
+  scan_apply_kernel<T><<<unsigned(tiles), kThreads, 0, s>>>(load, data, n, partial, unsigned(tiles), self_prefix, co);
   FGS_LAUNCH_CHECK("scan_apply_kernel");
   return FGS_OK;
+}
+
+template <typename T>
+static int exclusive_scan(T *data, uint64_t n, T *scratch, hipStream_t s, CountOut co = CountOut{}) {
+  return exclusive_scan_of<T>(ScanArray<T>{data}, data, n, scratch, s, co);
 }
 
 int exclusive_scan_u32(uint32_t *data, uint64_t n, uint32_t *scratch, hipStream_t s) {
@@ -387,8 +410,9 @@ int scan_counts(uint32_t *count, uint64_t n, uint32_t *scratch, uint64_t cap, un
   return exclusive_scan<uint32_t>(count, n, scratch, s, CountOut{cap, total, pairs, overflow});
 }
 
-int exclusive_scan_u64(uint64_t *data, uint64_t n, uint32_t *scratch, hipStream_t s) {
-  return exclusive_scan<uint64_t>(data, n, reinterpret_cast<uint64_t *>(scratch), s);
+int exclusive_scan_quantized(const float *v, const float *vmax, uint64_t *out, uint64_t n, uint32_t *scratch,
+                             hipStream_t s) {
+  return exclusive_scan_of<uint64_t>(ScanQuantized{v, vmax}, out, n, reinterpret_cast<uint64_t *>(scratch), s);
 }
 
 uint64_t sort_scratch_words(uint64_t n) {
