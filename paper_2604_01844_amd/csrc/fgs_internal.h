@@ -75,6 +75,18 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t n) {
   return x * base + (x < rem ? x : rem) + q;
 }
 
+// As xcd_block, in runs of kXcdRun blocks that the XCDs take in turn: where
+// the work is uneven over the grid (Gaussians in a body, empty tiles around
+// it) every XCD gets its share of it, and neighbours within a run still share
+// an L2. The blocks past the last whole round keep their number.
+constexpr uint32_t kXcdRun = 16;
+__device__ __forceinline__ uint32_t xcd_run_block(uint32_t b, uint32_t n) {
+  constexpr uint32_t kRound = kXcds * kXcdRun;
+  const uint32_t r = b / kRound, i = b - r * kRound;
+  if ((r + 1u) * kRound > n) return b;
+  return r * kRound + (i % kXcds) * kXcdRun + i / kXcds;
+}
+
 // Calls f(std::integral_constant<int, TPB>) with TPB = tiles_per_block(n_tiles, small_blocks).
 template <typename F>
 void with_tiles_per_block(uint64_t n_tiles, F &&f, bool small_blocks = false) {
@@ -252,6 +264,31 @@ __device__ __forceinline__ float block_sum_f32(float v, float *sh) {
     t = w[0];
   }
   return t;
+}
+
+// acc[k] += w ex[k] for the k whose arg[k] >= thr, for eight k at a time, every
+// lane by itself: the compare writes the execution mask and the FMA runs under
+// it, so the cutoff costs one vector instruction per term (the mask is put
+// back by the scalar unit) where compare and select cost two. The terms left
+// out are not added at all (a select adds w times zero). The first instruction
+// reads no ex: a v_exp_f32 right before it has its wait.
+__device__ __forceinline__ void masked_fma8(float (&acc)[8], float w, const float (&arg)[8], const float (&ex)[8],
+                                            float thr) {
+  uint64_t mask;
+#define FGS_TERM(a, x, e)                \
+  "v_cmpx_ge_f32 vcc, %" #a ", %26\n\t" \
+  "v_fmac_f32 %" #x ", %25, %" #e "\n\t" \
+  "s_mov_b64 exec, %8\n\t"
+  asm volatile(
+      "s_mov_b64 %8, exec\n\t" FGS_TERM(9, 0, 17) FGS_TERM(10, 1, 18) FGS_TERM(11, 2, 19) FGS_TERM(12, 3, 20)
+          FGS_TERM(13, 4, 21) FGS_TERM(14, 5, 22) FGS_TERM(15, 6, 23) FGS_TERM(16, 7, 24)
+      : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6]),
+        "+v"(acc[7]), "=&s"(mask)
+      : "v"(arg[0]), "v"(arg[1]), "v"(arg[2]), "v"(arg[3]), "v"(arg[4]), "v"(arg[5]), "v"(arg[6]), "v"(arg[7]),
+        "v"(ex[0]), "v"(ex[1]), "v"(ex[2]), "v"(ex[3]), "v"(ex[4]), "v"(ex[5]), "v"(ex[6]), "v"(ex[7]), "v"(w),
+        "v"(thr)
+      : "vcc");
+#undef FGS_TERM
 }
 
 // log2(e): exp(x) = exp2(x * log2(e)). Kernels pre-scale quadratic forms by

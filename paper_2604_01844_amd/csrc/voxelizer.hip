@@ -386,6 +386,312 @@ __global__ __launch_bounds__(kWave * TPB) void vox_fwd_kernel(const uint32_t *__
   }
 }
 
+// ---------------------------------------------------------- large grids
+//
+// On grids with a wave per tile (no chunks) the forward sorts a tile's pairs
+// by quarter of the tile (8 x 4 x 4 voxels, whole x-rows) before evaluating
+// them: a quarter that the support does not reach is skipped, one that lies
+// inside the support altogether ("interior") needs no cutoff test, and only
+// the rest ("boundary") is evaluated as vox_fwd_kernel does. Both decisions
+// come from the value and the gradient of the exponent at the quarter's
+// centre: the form is concave, so its tangent plane bounds it from above
+// (skip), and its value less every term's largest drop bounds it from below
+// (interior). Both keep a margin of 0.1% of the kappa cutoff, far above
+// rounding, so every voxel keeps the decision that the per-voxel test makes.
+
+// Tiles per Gaussian from which the forward evaluates interior quarters by
+// products along the row (vox_fwd_product_kernel).
+// Products pay where most quarters are interior: with sigma 15 voxels (1,100
+// tiles per Gaussian) two thirds are and the forward takes 37.3 ms against
+// 47 in list order (500,000 Gaussians, 512^3); with sigma 3 (20 tiles) a tenth
+// are, and the two lists per quarter cost more than they save (1.23 against
+// 0.65 ms, 200,000 at 256^3). They change the order of the sums.
+constexpr uint64_t kProductKeysPerRecord = 96;
+
+// A pair's exponent over the tile, arg(k, Y, Z) = a00 + a10 Y + a01 Z + a20 Y^2
+// + a11 Y Z + a02 Z^2 + k (e0 + e1 Y + e2 Z) + c k^2 for voxel k of the x-row
+// (Y, Z), half-integers from the tile's centre.
+struct TilePoly {
+  float a00, a10, a01, e0;
+  float g[3];  // gradient at the centre
+  float q;     // value at the centre
+};
+
+__device__ __forceinline__ TilePoly tile_poly(const float4 &p, const float4 &c0, const float4 &c1, float ox, float oy,
+                                              float oz) {
+  TilePoly T;
+  const float dx = ox - p.x, dy = oy - p.y, dz = oz - p.z;
+  const float hx = fmaf(c0.y, dy, c0.z * dz), hy = fmaf(c1.x, dz, c0.w * dy);
+  T.q = fmaf(dx, fmaf(c0.x, dx, hx), fmaf(dy, hy, c1.y * dz * dz));
+  T.g[0] = fmaf(2.f * c0.x, dx, hx);
+  T.g[1] = fmaf(c0.y, dx, fmaf(2.f * c0.w, dy, c1.x * dz));
+  T.g[2] = fmaf(c0.z, dx, fmaf(c1.x, dy, 2.f * c1.y * dz));
+  const float h = 0.5f * (kVT - 1);
+  T.a00 = fmaf(h * h, c0.x, fmaf(-h, T.g[0], T.q));
+  T.a10 = fmaf(-h, c0.y, T.g[1]);
+  T.a01 = fmaf(-h, c0.z, T.g[2]);
+  T.e0 = fmaf(-2.f * h, c0.x, T.g[0]);
+  return T;
+}
+
+// Bits Q: quarter Q = (y half) + 2 (z half) reached by the support; interior.
+__device__ __forceinline__ void quarter_masks(const TilePoly &T, const float4 &c0, const float4 &c1, float thr_cull,
+                                              float thr_int, uint32_t &reach, uint32_t &inner) {
+  // half-extents of a quarter's voxel centres: 3.5, 1.5, 1.5; its centre is at Y, Z = +-2
+  const float drop = fmaf(12.25f, fabsf(c0.x), fmaf(2.25f, fabsf(c0.w) + fabsf(c1.y),
+                          fmaf(5.25f, fabsf(c0.y) + fabsf(c0.z), 2.25f * fabsf(c1.x))));
+  reach = inner = 0;
+#pragma unroll
+  for (int Q = 0; Q < 4; ++Q) {
+    const float Y = (Q & 1) ? 2.f : -2.f, Z = (Q >> 1) ? 2.f : -2.f;
+    const float gx = fmaf(c0.y, Y, fmaf(c0.z, Z, T.g[0]));
+    const float gy = fmaf(2.f * c0.w, Y, fmaf(c1.x, Z, T.g[1]));
+    const float gz = fmaf(c1.x, Y, fmaf(2.f * c1.y, Z, T.g[2]));
+    const float q = fmaf(Y, fmaf(c0.w, Y, fmaf(c1.x, Z, T.g[1])), fmaf(Z, fmaf(c1.y, Z, T.g[2]), T.q));
+    const float slope = fmaf(3.5f, fabsf(gx), 1.5f * (fabsf(gy) + fabsf(gz)));
+    if (!(q + slope < thr_cull)) reach |= 1u << Q;
+    if (q - slope - drop >= thr_int) inner |= 1u << Q;
+  }
+  // the products along a row stay far from the ends of FP32's range: their
+  // exponent is at most |threshold| + 49 |c|
+  inner &= (thr_int > -64.f && c0.x > -0.75f) ? reach : 0u;
+}
+
+// The quarters' lists of a batch of 64 pairs: slots whose bit Q of mask is
+// set, in slot order, padded with the null slot to an even common length,
+// which is returned. s_list: [4][kWave].
+__device__ __forceinline__ int quarter_lists(uint32_t mask, int lane, uint8_t *s_list) {
+  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  int n[4], most = 0;
+#pragma unroll
+  for (int Q = 0; Q < 4; ++Q) {
+    const bool bit = (mask >> Q) & 1u;
+    const uint64_t bal = __ballot(bit);
+    if (bit) s_list[Q * kWave + __popcll(bal & lt)] = uint8_t(lane);
+    n[Q] = __popcll(bal);
+    most = max(most, n[Q]);
+  }
+  most = (most + 1) & ~1;
+#pragma unroll
+  for (int Q = 0; Q < 4; ++Q)
+    if (lane >= n[Q] && lane < most) s_list[Q * kWave + lane] = uint8_t(kWave);
+  return most;
+}
+
+// One wave per 8^3 tile; 16-lane group Q owns quarter Q, each lane one x-row
+// of 8 voxels, and walks its list of reached pairs in list order: the sums
+// are vox_fwd_kernel's, bit for bit. Bound by VALU issue. Measured with
+// 200,000 Gaussians at 256^3 in a body (sigma 3 voxels): 1.35 ms with whole
+// tiles, compare and select, and a contiguous eighth of the grid per XCD; 0.65
+// ms now (the runs of blocks per XCD matter as much as the quarters there).
+template <int TPB>
+__global__ __launch_bounds__(kWave * TPB) void vox_fwd_ordered_kernel(const uint32_t *__restrict__ start,
+                                                                      const uint32_t *__restrict__ svals,
+                                                                      const float4 *__restrict__ prho,
+                                                                      const float4 *__restrict__ a0,
+                                                                      const float4 *__restrict__ a1,
+                                                                      const uint32_t *__restrict__ gid, GridDev G,
+                                                                      uint32_t n_tiles, float thr_widen,
+                                                                      float *__restrict__ vol) {
+  // slot kWave: a pair that adds nothing
+  __shared__ float4 s_all[TPB][3][kWave + 1];
+  __shared__ uint8_t s_list_all[TPB][4 * kWave];
+  const int wid = threadIdx.x / kWave;
+  float4 *s_p = s_all[wid][0], *s_a0 = s_all[wid][1], *s_a1 = s_all[wid][2];
+  const uint32_t tile = xcd_run_block(blockIdx.x, gridDim.x) * TPB + wid;
+  if (tile >= n_tiles) return;
+  const int tx = int(tile % uint32_t(G.nt[0]));
+  const int tyz = int(tile / uint32_t(G.nt[0]));
+  const int ty = tyz % G.nt[1];
+  const int tz = tyz / G.nt[1];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int grp = lane >> 4;
+  const int y = ty * kVT + (grp & 1) * 4 + (lane & 3), z = tz * kVT + (grp >> 1) * 4 + ((lane >> 2) & 3);
+  const float fx0 = float(tx * kVT), fy = float(y), fz = float(z);
+  const float h = 0.5f * (kVT - 1);
+  if (lane == 0) {
+    s_p[kWave] = s_a0[kWave] = make_float4(0.f, 0.f, 0.f, 0.f);
+    s_a1[kWave] = make_float4(0.f, 0.f, INFINITY, 0.f);  // threshold above every exponent
+  }
+  float acc[kVT];
+#pragma unroll
+  for (int k = 0; k < kVT; ++k) acc[k] = 0.f;
+  const uint32_t e = start[tile + 1];
+  for (uint32_t b = start[tile]; b < e; b += kWave) {
+    uint32_t reach = 0, inner = 0;
+    if (b + lane < e) {
+      const uint32_t r = gid[svals[b + lane]];
+      const float4 p = prho[r], c0 = a0[r], c1 = a1[r];
+      const TilePoly T = tile_poly(p, c0, c1, fx0 + h, float(ty * kVT) + h, float(tz * kVT) + h);
+      quarter_masks(T, c0, c1, c1.z + thr_widen, c1.z - thr_widen, reach, inner);
+      s_p[lane] = p;
+      s_a0[lane] = c0;
+      s_a1[lane] = c1;
+    }
+    const int n = quarter_lists(reach, lane, s_list_all[wid]);
+    wave_lds_sync();
+    const uint8_t *list = s_list_all[wid] + grp * kWave;
+    for (int i = 0; i < n; ++i) {
+      const int j = int(list[i]);
+      const float4 p = s_p[j], c0 = s_a0[j], c1 = s_a1[j];
+      const float dy = fy - p.y, dz = fz - p.z;
+      const float B = fmaf(c0.y, dy, c0.z * dz);
+      const float Cc = fmaf(dy, fmaf(c0.w, dy, c1.x * dz), c1.y * dz * dz);
+      const float dx0 = fx0 - p.x;
+      const float arg0 = fmaf(dx0, fmaf(c0.x, dx0, B), Cc);
+      const float E = fmaf(2.f * c0.x, dx0, B);
+      float arg[kVT], ex[kVT];
+#pragma unroll
+      for (int k = 0; k < kVT; ++k) {
+        const float fk = float(k);
+        arg[k] = (k == 0) ? arg0 : fmaf(fk, fmaf(c0.x, fk, E), arg0);
+        ex[k] = __builtin_amdgcn_exp2f(arg[k]);
+      }
+      masked_fma8(acc, p.w, arg, ex, c1.z);
+    }
+    wave_lds_sync();
+  }
+  if (y < G.dims[1] && z < G.dims[2]) {
+    float *row = vol + (uint64_t(z) * G.dims[1] + y) * uint64_t(G.dims[0]);
+#pragma unroll
+    for (int k = 0; k < kVT; ++k) {
+      const int x = tx * kVT + k;
+      if (x < G.dims[0]) row[x] = acc[k];
+    }
+  }
+}
+
+// One wave per 8^3 tile; 16-lane group Q owns quarter Q and walks its lists,
+// its two 8-lane halves taking two entries at a time, each lane two x-rows
+// (one y, two z) of 8 voxels; the halves' sums of the same voxels are added
+// once at the end. Interior entries: exp2 of the row's first exponent and of
+// its first step, then a voxel costs a product, p_{k+1} = p_k R, and an FMA
+// with the pair's rho exp2(c k^2) (its eight values computed once per pair by
+// the lane that stages it), 3.4 instructions per voxel with the row's share
+// against 8.4 for the boundary path (v_exp_f32 takes two issue slots), whose
+// arithmetic is vox_fwd_kernel's. Bound by VALU issue. Measured with
+// 500,000 Gaussians at 512^3 (sigma 15 voxels): 54.3 ms with a whole tile per
+// pair and compare and select, 37.3 ms now.
+template <int TPB>
+__global__ __launch_bounds__(kWave * TPB) void vox_fwd_product_kernel(const uint32_t *__restrict__ start,
+                                                                      const uint32_t *__restrict__ svals,
+                                                                      const float4 *__restrict__ prho,
+                                                                      const float4 *__restrict__ a0,
+                                                                      const float4 *__restrict__ a1,
+                                                                      const uint32_t *__restrict__ gid, GridDev G,
+                                                                      uint32_t n_tiles, float thr_widen,
+                                                                      float *__restrict__ vol) {
+  // per batch slot (slot kWave: a pair that adds nothing): the form's
+  // coefficients, the tile polynomial, rho exp2(c k^2), and (p, rho)
+  __shared__ float4 s_all[TPB][6][kWave + 1];
+  __shared__ uint8_t s_list_all[TPB][2][4 * kWave];
+  const int wid = threadIdx.x / kWave;
+  float4 *s_c = s_all[wid][0], *s_d = s_all[wid][1], *s_t = s_all[wid][2], *s_e = s_all[wid][3],
+         *s_f = s_all[wid][4], *s_p = s_all[wid][5];
+  const uint32_t tile = xcd_run_block(blockIdx.x, gridDim.x) * TPB + wid;
+  if (tile >= n_tiles) return;
+  const int tx = int(tile % uint32_t(G.nt[0]));
+  const int tyz = int(tile / uint32_t(G.nt[0]));
+  const int ty = tyz % G.nt[1];
+  const int tz = tyz / G.nt[1];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int grp = lane >> 4, half = (lane >> 3) & 1;
+  const int ly = (grp & 1) * 4 + (lane & 3), lz = (grp >> 1) * 4 + ((lane >> 2) & 1) * 2;
+  const int y = ty * kVT + ly, z = tz * kVT + lz;
+  const float fx0 = float(tx * kVT), fy = float(y), fz = float(z);
+  const float h = 0.5f * (kVT - 1);
+  const float Y = float(ly) - h, Z = float(lz) - h;
+  const float ox = fx0 + h, oy = float(ty * kVT) + h, oz = float(tz * kVT) + h;
+  if (lane == 0) {
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    s_c[kWave] = s_t[kWave] = s_e[kWave] = s_f[kWave] = s_p[kWave] = zero;
+    s_d[kWave] = make_float4(0.f, 0.f, INFINITY, 0.f);  // threshold above every exponent
+  }
+  float acc[2][kVT];
+#pragma unroll
+  for (int k = 0; k < kVT; ++k) acc[0][k] = acc[1][k] = 0.f;
+  const uint32_t e = start[tile + 1];
+  for (uint32_t b = start[tile]; b < e; b += kWave) {
+    uint32_t reach = 0, inner = 0;
+    if (b + lane < e) {
+      const uint32_t r = gid[svals[b + lane]];
+      const float4 p = prho[r], c0 = a0[r], c1 = a1[r];
+      const TilePoly T = tile_poly(p, c0, c1, ox, oy, oz);
+      quarter_masks(T, c0, c1, c1.z + thr_widen, c1.z - thr_widen, reach, inner);
+      s_c[lane] = make_float4(c0.y, c0.z, c0.w, c1.x);
+      s_d[lane] = make_float4(c1.y, c0.x, c1.z, 0.f);
+      s_p[lane] = p;
+      if (inner) {
+        s_t[lane] = make_float4(T.a00, T.a10, T.a01, T.e0);
+        s_e[lane] = make_float4(p.w, p.w * __builtin_amdgcn_exp2f(c0.x), p.w * __builtin_amdgcn_exp2f(4.f * c0.x),
+                                p.w * __builtin_amdgcn_exp2f(9.f * c0.x));
+        s_f[lane] = make_float4(p.w * __builtin_amdgcn_exp2f(16.f * c0.x), p.w * __builtin_amdgcn_exp2f(25.f * c0.x),
+                                p.w * __builtin_amdgcn_exp2f(36.f * c0.x), p.w * __builtin_amdgcn_exp2f(49.f * c0.x));
+      }
+    }
+    const int n_in = quarter_lists(inner, lane, s_list_all[wid][0]);
+    const int n_bd = quarter_lists(reach & ~inner, lane, s_list_all[wid][1]);
+    wave_lds_sync();
+    const uint8_t *l_in = s_list_all[wid][0] + grp * kWave + half, *l_bd = s_list_all[wid][1] + grp * kWave + half;
+    for (int i = 0; i < n_in; i += 2) {
+      const int j = int(l_in[i]);
+      const float4 c = s_c[j], d = s_d[j], t = s_t[j], u = s_e[j], v = s_f[j];
+      const float C[kVT] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+      const float ay = fmaf(Y, fmaf(c.z, Y, t.y), t.x);  // a00 + a10 Y + a20 Y^2
+      const float az = fmaf(c.w, Y, t.z);                // a01 + a11 Y
+      const float ey = fmaf(c.x, Y, t.w);                // e0 + e1 Y
+#pragma unroll
+      for (int w = 0; w < 2; ++w) {
+        const float Zw = Z + float(w);
+        float pk = __builtin_amdgcn_exp2f(fmaf(Zw, fmaf(d.x, Zw, az), ay));
+        const float R = __builtin_amdgcn_exp2f(fmaf(c.y, Zw, ey));
+        acc[w][0] = fmaf(pk, C[0], acc[w][0]);
+#pragma unroll
+        for (int k = 1; k < kVT; ++k) {
+          pk *= R;
+          acc[w][k] = fmaf(pk, C[k], acc[w][k]);
+        }
+      }
+    }
+    for (int i = 0; i < n_bd; i += 2) {
+      const int j = int(l_bd[i]);
+      const float4 c = s_c[j], d = s_d[j], p = s_p[j];
+      const float dy = fy - p.y, dx0 = fx0 - p.x;
+#pragma unroll
+      for (int w = 0; w < 2; ++w) {
+        const float dz = (fz + float(w)) - p.z;
+        const float B = fmaf(c.x, dy, c.y * dz);
+        const float Cc = fmaf(dy, fmaf(c.z, dy, c.w * dz), d.x * dz * dz);
+        const float arg0 = fmaf(dx0, fmaf(d.y, dx0, B), Cc);
+        const float E = fmaf(2.f * d.y, dx0, B);
+        float arg[kVT], ex[kVT];
+#pragma unroll
+        for (int k = 0; k < kVT; ++k) {
+          const float fk = float(k);
+          arg[k] = (k == 0) ? arg0 : fmaf(fk, fmaf(d.y, fk, E), arg0);
+          ex[k] = __builtin_amdgcn_exp2f(arg[k]);
+        }
+        masked_fma8(acc[w], p.w, arg, ex, d.z);
+      }
+    }
+    wave_lds_sync();
+  }
+  // half 0 adds half 1's sums of the same rows (lane + 8); half 0 writes the first row, half 1 the second
+#pragma unroll
+  for (int w = 0; w < 2; ++w)
+#pragma unroll
+    for (int k = 0; k < kVT; ++k) acc[w][k] += __shfl_xor(acc[w][k], 8, kWave);
+  const int zw = z + half;
+  if (y < G.dims[1] && zw < G.dims[2]) {
+    float *row = vol + (uint64_t(zw) * G.dims[1] + y) * uint64_t(G.dims[0]);
+#pragma unroll
+    for (int k = 0; k < kVT; ++k) {
+      const int x = tx * kVT + k;
+      if (x < G.dims[0]) row[x] = half ? acc[1][k] : acc[0][k];
+    }
+  }
+}
+
 // Backward over one 8^3 tile: lane j owns pair (tile, list[j]) and sums the
 // ten moments over the 512 voxels. Coordinates are relative to the tile
 // centre, (cx, cy, cz) in {-3.5, ..., 3.5}; along each x-row the exponent is
@@ -842,6 +1148,16 @@ int vox_forward(const fgs_gaussians *g, const fgs_grid *grid, const fgs_opts *op
   hipEvent_t *ev = static_cast<hipEvent_t *>(opts->events);
   if (ev) FGS_HIP(hipEventRecord(ev[0], s));
   const uint64_t units = L.T * uint64_t(chunks);
+  const float thr_widen = -0.5f * kLog2e * opts->kappa * opts->kappa * (kCullSlack - 1.f);
+  if (chunks == 1 && !(ws->key_capacity == 0 && L.K >= kProductKeysPerRecord * L.N)) {
+    vox_fwd_ordered_kernel<4><<<grid_for(L.T, 4), kWave * 4, 0, s>>>(
+        at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
+        at<uint32_t>(b, L.gid), G, uint32_t(L.T), thr_widen, vol);
+  } else if (chunks == 1) {
+    vox_fwd_product_kernel<4><<<grid_for(L.T, 4), kWave * 4, 0, s>>>(
+        at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
+        at<uint32_t>(b, L.gid), G, uint32_t(L.T), thr_widen, vol);
+  } else
   with_tiles_per_block(units, [&](auto tpb) {
     constexpr int TPB = decltype(tpb)::value;
     vox_fwd_kernel<false, TPB><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
