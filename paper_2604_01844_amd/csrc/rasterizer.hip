@@ -18,15 +18,15 @@
 //                         ascending Gaussian index; no depth key (the sum is
 //                         order-free).
 //   5. ranges kernel      per-(view, tile) [start, end) by boundary detection.
-//   6. splat kernel       one 64-lane wave per 16x16 tile, up to 16 tiles
-//                         per workgroup; batches of 64 records staged in LDS;
+//   6. splat kernel       one 64-lane wave per 16x16 tile, up to 4 tiles per
+//                         workgroup; batches of 64 records staged in LDS;
 //                         each record is tested against the tile's four 8x8
 //                         quadrants and a 16-lane group walks one quadrant's
-//                         list, each lane a column of 4 pixels; the Gaussian
+//                         list, each lane a column of 8 pixels; the Gaussian
 //                         factor is one v_exp_f32 of a pre-scaled quadratic
-//                         form; support test d^2 <= k^2 (skipped for
+//                         form with the support test d^2 <= k^2, or, for
 //                         quadrants entirely inside the support when
-//                         Gaussians span many tiles).
+//                         Gaussians span many tiles, products down the column.
 // Backward (per-Gaussian formulation, Sec. 3.5):
 //   7. splat-grad kernel  same tiling and quadrant lists; one lane per
 //                         (quadrant, Gaussian) pair sums over the quadrant's
@@ -587,66 +587,93 @@ __device__ __forceinline__ void build_quad_lists(uint32_t mask, int lane, uint8_
 }
 
 // Interior quadrants: every pixel centre of the quadrant lies inside the
-// support, so the per-pixel cutoff test can be skipped. The pre-scaled form
-// is concave, so its smallest value over the quadrant's pixel-centre square
-// is at one of the four corners; thr_int is a hair above the support
-// threshold (kInteriorSlack), so FP32 rounding of the per-pixel exponent
-// cannot take an interior pixel below thr.
+// support, so the per-pixel cutoff test can be skipped and the exponential
+// taken once per column instead of once per pixel. Where a call splits its
+// pairs so, both decisions come from the value and the gradient of the
+// pre-scaled form at the quadrant's centre: the form is concave, so its
+// tangent plane bounds it from above (not reached), and its value less every
+// term's largest drop bounds it from below (interior). Both keep a margin of
+// 0.1% of the kappa cutoff (margin < 0), far above the rounding of the
+// per-pixel exponent, so every pixel keeps the decision of the per-pixel test.
 //
-// The forward uses it (each 16-lane group takes its quadrant's interior
-// pairs first; iterations where all four groups hold interior pairs run
-// without the select). The test and the split lists cost a few percent per
-// batch, so this pays off only when most pairs are interior, i.e. when
-// Gaussians span many tiles: the forward takes the interior path when a call
-// averages at least kInteriorKeysPerRecord tiles per record. Measured on
-// MI355X: at about 17 tiles per record (50k Gaussians, 512^2 views) 37% of
-// the iterations are all-interior and the kernel gets ~8% slower; at about
-// 180 (500k Gaussians, 2048^2 views) 77% are, and it gets 7% faster.
-constexpr float kInteriorSlack = 0.999f;
+// Splitting pays when most quadrants are interior, i.e. when Gaussians span
+// many tiles: a call does it when it averages at least kSplitKeysPerRecord
+// tiles per record. A call that read its pair count back knows; at a fixed key
+// capacity the kernel reads the count on the device, unless the capacity
+// itself is below the line, so both take the same path for the same pairs.
+// Measured: at 17 tiles per record (sigma 7 pixels) the forward gains a fifth;
+// at 6 (sigma 4) a fifth of the quadrants is interior and the second set of
+// lists costs what it saves.
+constexpr uint64_t kSplitKeysPerRecord = 16;
+enum SplitMode { kSplitNever, kSplitAlways, kSplitByCount };
 
-// Workgroup size of the splat kernels in large calls. The backward takes 4
-// tiles per workgroup always; the forward does when a call averages at least
-// kSmallBlockKeysPerTile keys per tile. Measured on MI355X: the backward is
-// 2% faster with 4 at about 720 keys per tile (75 views of 512^2, 50k
-// Gaussians) and 11% at about 5,700 (10 views of 2048^2, 500k Gaussians);
-// the forward is 3% slower with 4 at 720 and 13% faster at 5,700.
-constexpr uint64_t kSmallBlockKeysPerTile = 2048;
-constexpr uint64_t kInteriorKeysPerRecord = 48;
-
-__device__ __forceinline__ uint32_t quad_interior(const float4 &c, float u, float v, float tx0, float ty0,
-                                                  float thr_int) {
-  uint32_t m = 0;
-#pragma unroll
-  for (int Q = 0; Q < 4; ++Q) {
-    const float dx0 = tx0 + float((Q & 1) * 8) - u, dy0 = ty0 + float((Q >> 1) * 8) - v;
-    float lo = 0.f;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float dx = dx0 + float((k & 1) * 7), dy = dy0 + float((k >> 1) * 7);
-      const float a = fmaf(dx, fmaf(c.x, dx, c.y * dy), c.z * dy * dy);
-      lo = (k == 0) ? a : fminf(lo, a);
-    }
-    if (lo >= thr_int) m |= 1u << Q;
-  }
-  return m;
+__device__ __forceinline__ bool split_pairs(const uint32_t *__restrict__ kdev, uint64_t n_records) {
+  return uint64_t(kdev[0]) >= kSplitKeysPerRecord * n_records;
 }
 
-// As build_quad_lists, with each quadrant's interior pairs (imask) first:
-// ni[Q] of the nq[Q] entries of list Q need no cutoff test.
-__device__ __forceinline__ void build_quad_lists_split(uint32_t mask, uint32_t imask, int lane,
-                                                       uint8_t (*s_list)[kWave], int nq[4], int ni[4]) {
-  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+inline SplitMode split_mode(uint64_t pairs, uint64_t n_records, bool is_capacity, bool no_cull) {
+  if (no_cull || pairs < kSplitKeysPerRecord * n_records) return kSplitNever;
+  return is_capacity ? kSplitByCount : kSplitAlways;
+}
+
+// Calls f(std::integral_constant<SplitMode, mode>).
+template <typename F>
+void with_split(SplitMode mode, F &&f) {
+  if (mode == kSplitNever)
+    f(std::integral_constant<SplitMode, kSplitNever>());
+  else if (mode == kSplitAlways)
+    f(std::integral_constant<SplitMode, kSplitAlways>());
+  else
+    f(std::integral_constant<SplitMode, kSplitByCount>());
+}
+
+// The form over the tile whose centre is (cx, cy): value q and gradient g there.
+struct TileForm {
+  float q, gx, gy;
+};
+
+__device__ __forceinline__ TileForm tile_form(const float4 &c, float u, float v, float cx, float cy) {
+  const float dx = cx - u, dy = cy - v;
+  TileForm T;
+  T.q = fmaf(dx, fmaf(c.x, dx, c.y * dy), c.z * dy * dy);
+  T.gx = fmaf(2.f * c.x, dx, c.y * dy);
+  T.gy = fmaf(2.f * c.z, dy, c.y * dx);
+  return T;
+}
+
+__device__ __forceinline__ void quad_split(const TileForm &T, const float4 &c, float thr, float margin,
+                                           uint32_t &reach, uint32_t &inner) {
+  const float drop = 12.25f * (fabsf(c.x) + fabsf(c.y) + fabsf(c.z));
+  reach = inner = 0;
 #pragma unroll
   for (int Q = 0; Q < 4; ++Q) {
-    const bool bi = (imask >> Q) & 1u;
-    const uint64_t bal_i = __ballot(bi);
-    if (bi) s_list[Q][__popcll(bal_i & lt)] = uint8_t(lane);
-    ni[Q] = __popcll(bal_i);
-    const bool bb = ((mask & ~imask) >> Q) & 1u;
-    const uint64_t bal_b = __ballot(bb);
-    if (bb) s_list[Q][ni[Q] + __popcll(bal_b & lt)] = uint8_t(lane);
-    nq[Q] = ni[Q] + __popcll(bal_b);
+    const float X = (Q & 1) ? 4.f : -4.f, Y = (Q >> 1) ? 4.f : -4.f;
+    const float gx = fmaf(2.f * c.x, X, fmaf(c.y, Y, T.gx)), gy = fmaf(2.f * c.z, Y, fmaf(c.y, X, T.gy));
+    const float q = fmaf(X, fmaf(c.x, X, fmaf(c.y, Y, T.gx)), fmaf(Y, fmaf(c.z, Y, T.gy), T.q));
+    const float slope = 3.5f * (fabsf(gx) + fabsf(gy));
+    if (!(q + slope < thr + margin)) reach |= 1u << Q;
+    if (q - slope - drop >= thr - margin) inner |= 1u << Q;
   }
+  // the products down a column stay far from the ends of FP32's range: their
+  // exponent is at most |threshold| + 49 |c|
+  inner &= (thr > -64.f && c.z > -0.75f && c.x > -0.75f) ? reach : 0u;
+}
+
+// Workgroup size: the splat kernels take at most 4 tiles per workgroup. The
+// backward is 2% faster with 4 than with 16 at about 720 keys per tile (75
+// views of 512^2, 50k Gaussians) and 11% at about 5,700 (2048^2, 500k).
+
+// The quadrants' lists of a batch: slots whose bit Q of mask is set, in slot
+// order, padded with the null slot (kWave) to an even common length, which is
+// returned.
+__device__ __forceinline__ int build_padded_lists(uint32_t mask, int lane, uint8_t (*s_list)[kWave]) {
+  int n[4], pos[4];
+  build_quad_lists(mask, lane, s_list, n, pos);
+  const int most = (max(max(n[0], n[1]), max(n[2], n[3])) + 1) & ~1;
+#pragma unroll
+  for (int Q = 0; Q < 4; ++Q)
+    if (lane >= n[Q] && lane < most) s_list[Q][lane] = uint8_t(kWave);
+  return most;
 }
 
 // The record indices of the sorted lists. Key/value lists hold them in the
@@ -716,25 +743,38 @@ __device__ __forceinline__ void set_null_record(float4 *s_cw, float2 *s_xy) {
 
 // kCount = true: instead of the image, count the (pixel, Gaussian) pairs in
 // the support whose pixel lies on the detector (the algorithmic work).
-// kTau: the density-aware support (per-record thresholds, read with each
-// pair); without it the pixel loop compares with the kernel argument.
-template <bool kCount, bool kInterior, int TPB, bool kTau>
-__global__ __launch_bounds__(kWave * TPB) void splat_fwd_kernel(const uint2 *__restrict__ rng,
+// Interior pairs of a split call: exp2 of the column's first exponent and of
+// its first step, then a pixel costs a product, p_{k+1} = p_k R, and an FMA
+// with the pair's w exp2(c11 k^2), whose eight values the lane that stages the
+// record computes once: 3.4 issue slots per pixel with the column's share,
+// against 7.2 for a pixel with its own exponential (two slots) and cutoff.
+// The cutoff is a masked FMA (masked_fma8). 4 waves of a workgroup: with the
+// split's five arrays 16 would leave a CU one workgroup. Bound by VALU issue.
+// Measured: 75 views of 512^2, 50,000 Gaussians 2.97 ms with an exponential,
+// compare and select per pixel, 2.38 ms now (two fifths of the quadrants are
+// interior); 4 views of 2048^2, 500,000 Gaussians 14.1 ms with interior pairs
+// that only left out the compare and select, 10.7 ms now (four fifths).
+template <bool kCount, SplitMode kSplit, int TPB>
+__global__ __launch_bounds__(kWave * TPB) __attribute__((amdgpu_waves_per_eu(7, 7))) void splat_fwd_kernel(const uint2 *__restrict__ rng,
                                                            const ListRecs svals,
                                                            const SplatRec *__restrict__ rec,
+                                                           const uint32_t *__restrict__ kdev, uint64_t n_records,
                                                            int tiles_x, int tpv, int W, int H,
                                                            uint32_t n_tiles, int n_chunks, Units U, float thr,
                                                            float log2_tau, int no_cull,
                                                            float *__restrict__ img,
                                                            unsigned long long *__restrict__ counter) {
-  // per batch slot: the conic and weight, and (centre, 2 c11, support
-  // threshold): one address, the second array at a fixed offset from the first
-  __shared__ float4 s_rec_all[TPB][2][kWave + 1];
-  __shared__ uint8_t s_list_all[TPB][4][kWave];
+  // per batch slot: the conic and weight; (centre, 2 c11, support threshold);
+  // for interior pairs the tile form and w exp2(c11 k^2)
+  constexpr int kArrays = kSplit == kSplitNever ? 2 : 5, kLists = kSplit == kSplitNever ? 1 : 2;
+  __shared__ float4 s_rec_all[TPB][kArrays][kWave + 1];
+  __shared__ uint8_t s_list_all[TPB][kLists][4][kWave];
   const int wid = threadIdx.x / kWave;
-  float4 *s_cw = s_rec_all[wid][0];
-  float4 *s_xy = s_rec_all[wid][1];
-  uint8_t(*s_list)[kWave] = s_list_all[wid];
+  float4 *s_cw = s_rec_all[wid][0], *s_xy = s_rec_all[wid][1], *s_q = s_rec_all[wid][kArrays / 2],
+         *s_e = s_rec_all[wid][kArrays - 2], *s_f = s_rec_all[wid][kArrays - 1];
+  uint8_t(*s_list)[kWave] = s_list_all[wid][0], (*s_inner)[kWave] = s_list_all[wid][kLists - 1];
+  const bool split = kSplit == kSplitAlways || (kSplit == kSplitByCount && split_pairs(kdev, n_records));
+  const float margin = thr * (kCullSlack - 1.f);
   // work unit: a piece of a tile's list (U.first), or (tile, chunk) where
   // chunk c takes batches c, c + n_chunks, ...; each writes its own partial
   // image when there are several per tile
@@ -776,9 +816,14 @@ __global__ __launch_bounds__(kWave * TPB) void splat_fwd_kernel(const uint2 *__r
   const float px = float(tx * kTS + col) + 0.5f;
   const float py = float(ty * kTS + row0) + 0.5f;
   const float tx0 = float(tx * kTS) + 0.5f, ty0 = float(ty * kTS) + 0.5f;
+  // this lane's column and first row from the tile's centre
+  const float X = float(col) - 7.5f, Y = float(row0) - 7.5f;
+  const float XX = X * X, XY = X * Y, YY = Y * Y;
+  const float ccx = tx0 + 7.5f, ccy = ty0 + 7.5f;
   if (lane == 0) {
     s_cw[kWave] = make_float4(-1.f, 0.f, -1.f, 0.f);
     s_xy[kWave] = make_float4(-1.0e4f, -1.0e4f, -2.f, 0.f);
+    if (kSplit != kSplitNever) s_q[kWave] = s_e[kWave] = s_f[kWave] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
   float acc[kFwdRows];
 #pragma unroll
@@ -789,7 +834,7 @@ __global__ __launch_bounds__(kWave * TPB) void splat_fwd_kernel(const uint2 *__r
   for (uint32_t b = b_first; b < e; b += stride) {
     const uint32_t m = min(uint32_t(kWave), e - b);
     pf.advance(svals, rec, b, stride, e, lane);
-    uint32_t mask = 0, imask = 0;
+    uint32_t mask = 0, inner = 0;
     if (uint32_t(lane) < m) {
       const float4 ra = pf.cur.a;
       const float2 rb = make_float2(pf.cur.b.x, pf.cur.b.y);
@@ -798,43 +843,39 @@ __global__ __launch_bounds__(kWave * TPB) void splat_fwd_kernel(const uint2 *__r
       const float thr_r = support_thr(thr, log2_tau, c.w);
       s_cw[lane] = c;
       s_xy[lane] = make_float4(q.x, q.y, 2.f * c.z, thr_r);
-      mask = no_cull ? 0xFu : quad_mask(c, q.x, q.y, tx0, ty0, thr_r * kCullSlack);
-      if (kInterior && !kCount) imask = quad_interior(c, q.x, q.y, tx0, ty0, thr_r * kInteriorSlack) & mask;
-    }
-    int nq[4], ni[4] = {0, 0, 0, 0};
-    if (kInterior && !kCount) {
-      build_quad_lists_split(mask, imask, lane, s_list, nq, ni);
-    } else {
-      int pos[4];
-      build_quad_lists(mask, lane, s_list, nq, pos);
-    }
-    const int n_max = max(max(nq[0], nq[1]), max(nq[2], nq[3]));
-    // the lists are padded with the null slot to n_max rounded up to even
-    const int n_pad = (n_max + 1) & ~1;
-#pragma unroll
-    for (int Q = 0; Q < 4; ++Q)
-      if (lane >= nq[Q] && lane < n_pad) s_list[Q][lane] = uint8_t(kWave);
-    // iterations in which every group's two pairs are interior skip the cutoff test
-    const int n_fast = (kInterior && !kCount) ? (min(min(ni[0], ni[1]), min(ni[2], ni[3])) & ~1) : 0;
-    wave_lds_sync();
-    for (int i = 0; i < n_fast; i += 2) {
-      const int j = int(s_list[grp][i + half]);
-      const float4 c = s_cw[j];
-      const float4 q = s_xy[j];
-      const float dx = px - q.x;
-      const float dy = py - q.y;
-      const float A = c.x * dx * dx;
-      const float B = c.y * dx;
-      const float arg0 = fmaf(dy, fmaf(c.z, dy, B), A);
-      const float E = fmaf(q.z, dy, B);
-#pragma unroll
-      for (int k = 0; k < kFwdRows; ++k) {
-        const float fk = float(k);
-        const float arg = (k == 0) ? arg0 : fmaf(fk, fmaf(c.z, fk, E), arg0);
-        acc[k] = fmaf(c.w, __builtin_amdgcn_exp2f(arg), acc[k]);
+      if (split) {
+        const TileForm T = tile_form(c, q.x, q.y, ccx, ccy);
+        quad_split(T, c, thr_r, margin, mask, inner);
+        if (inner) {
+          s_q[lane] = make_float4(T.q, T.gx, T.gy, 0.f);
+          s_e[lane] = make_float4(c.w, c.w * __builtin_amdgcn_exp2f(c.z), c.w * __builtin_amdgcn_exp2f(4.f * c.z),
+                                  c.w * __builtin_amdgcn_exp2f(9.f * c.z));
+          s_f[lane] = make_float4(c.w * __builtin_amdgcn_exp2f(16.f * c.z), c.w * __builtin_amdgcn_exp2f(25.f * c.z),
+                                  c.w * __builtin_amdgcn_exp2f(36.f * c.z), c.w * __builtin_amdgcn_exp2f(49.f * c.z));
+        }
+      } else {
+        mask = no_cull ? 0xFu : quad_mask(c, q.x, q.y, tx0, ty0, thr_r * kCullSlack);
       }
     }
-    for (int i = n_fast; i < n_max; i += 2) {
+    // the lists are padded with the null slot to a common even length
+    const int n_in = split ? build_padded_lists(inner, lane, s_inner) : 0;
+    const int n_max = build_padded_lists(mask & ~inner, lane, s_list);
+    wave_lds_sync();
+    for (int i = 0; i < n_in; i += 2) {
+      const int j = int(s_inner[grp][i + half]);
+      const float4 c = s_cw[j], t = s_q[j], u = s_e[j], v = s_f[j];
+      const float C[kFwdRows] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+      const float arg0 = fmaf(t.y, X, fmaf(t.z, Y, fmaf(c.x, XX, fmaf(c.y, XY, fmaf(c.z, YY, t.x)))));
+      float pk = __builtin_amdgcn_exp2f(arg0);
+      const float R = __builtin_amdgcn_exp2f(fmaf(2.f * c.z, Y, fmaf(c.y, X, t.z)));
+      acc[0] = fmaf(pk, C[0], acc[0]);
+#pragma unroll
+      for (int k = 1; k < kFwdRows; ++k) {
+        pk *= R;
+        acc[k] = fmaf(pk, C[k], acc[k]);
+      }
+    }
+    for (int i = 0; i < n_max; i += 2) {
       const int j = int(s_list[grp][i + half]);
       const float4 c = s_cw[j];
       const float4 q = s_xy[j];
@@ -846,18 +887,15 @@ __global__ __launch_bounds__(kWave * TPB) void splat_fwd_kernel(const uint2 *__r
       // arg(dy + k) = arg0 + k (2 c.z dy + B) + c.z k^2
       const float arg0 = fmaf(dy, fmaf(c.z, dy, B), A);
       const float E = fmaf(q.z, dy, B);
+      float arg[kFwdRows], ex[kFwdRows];
 #pragma unroll
       for (int k = 0; k < kFwdRows; ++k) {
         const float fk = float(k);
-        const float arg = (k == 0) ? arg0 : fmaf(fk, fmaf(c.z, fk, E), arg0);
-        const float cut = kTau ? q.w : thr;
-        if (kCount) {
-          acc[k] += (arg >= cut) ? 1.f : 0.f;
-        } else {
-          const float ex = __builtin_amdgcn_exp2f(arg);
-          acc[k] = fmaf(c.w, (arg >= cut) ? ex : 0.f, acc[k]);
-        }
+        arg[k] = (k == 0) ? arg0 : fmaf(fk, fmaf(c.z, fk, E), arg0);
+        if (kCount) acc[k] += (arg[k] >= q.w) ? 1.f : 0.f;
+        else ex[k] = __builtin_amdgcn_exp2f(arg[k]);
       }
+      if (!kCount) masked_fma8(acc, c.w, arg, ex, q.w);
     }
     wave_lds_sync();
   }
@@ -2062,23 +2100,18 @@ extern "C" int fgs_project_views_fwd(const fgs_gaussians *g, const fgs_geom *geo
     const Units U = make_units(L, b, use_units(T, false));
     const uint64_t units = U.first ? L.n_units : L.T;
     const int no_cull = (opts->ablate & FGS_ABLATE_QUADRANT_CULL) ? 1 : 0;
-    const bool interior = L.K >= kInteriorKeysPerRecord * L.R;
-    const bool tau = opts->density_aabb_tau > 0.f;
-    with_tiles_per_block(units, [&](auto tpb) {
+    auto launch = [&](auto mode, auto tpb) {
       constexpr int TPB = decltype(tpb)::value;
-      if (tau)
-        splat_fwd_kernel<false, false, TPB, true><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
-            at<uint2>(b, L.rng), sv, at<SplatRec>(b, L.rec), tg.tiles_x, tg.tpv, geom->det_w, geom->det_h,
-            uint32_t(L.T), 1, U, thr, log2_tau, no_cull, part, nullptr);
-      else if (interior)
-        splat_fwd_kernel<false, true, TPB, false><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
-            at<uint2>(b, L.rng), sv, at<SplatRec>(b, L.rec), tg.tiles_x, tg.tpv, geom->det_w, geom->det_h,
-            uint32_t(L.T), 1, U, thr, log2_tau, no_cull, part, nullptr);
+      splat_fwd_kernel<false, decltype(mode)::value, TPB><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
+          at<uint2>(b, L.rng), sv, at<SplatRec>(b, L.rec), at<uint32_t>(b, L.kdev), L.R, tg.tiles_x, tg.tpv,
+          geom->det_w, geom->det_h, uint32_t(L.T), 1, U, thr, log2_tau, no_cull, part, nullptr);
+    };
+    with_split(split_mode(L.K, L.R, ws->key_capacity > 0, no_cull != 0), [&](auto mode) {
+      if (tiles_per_block(units) > 1)
+        launch(mode, std::integral_constant<int, 4>());
       else
-        splat_fwd_kernel<false, false, TPB, false><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
-            at<uint2>(b, L.rng), sv, at<SplatRec>(b, L.rec), tg.tiles_x, tg.tpv, geom->det_w, geom->det_h,
-            uint32_t(L.T), 1, U, thr, log2_tau, no_cull, part, nullptr);
-    }, L.K >= kSmallBlockKeysPerTile * L.T);
+        launch(mode, std::integral_constant<int, 1>());
+    });
     FGS_LAUNCH_CHECK("splat_fwd_kernel");
     if (U.first) {
       sum_units_kernel<<<grid_for(n_img, 256), 256, 0, s>>>(part, U.first, tg.tiles_x, tg.tpv, geom->det_w,
@@ -2123,17 +2156,9 @@ extern "C" int fgs_project_views_support(const fgs_gaussians *g, const fgs_geom 
   }
   const Units U = make_units(L, b, use_units(L.T, false));
   const uint64_t sunits = U.first ? L.n_units : L.T;
-  with_tiles_per_block(sunits, [&](auto tpb) {
-    constexpr int TPB = decltype(tpb)::value;
-    if (opts->density_aabb_tau > 0.f)
-      splat_fwd_kernel<true, false, TPB, true><<<grid_for(sunits, TPB), kWave * TPB, 0, s>>>(
-          at<uint2>(b, L.rng), sv, at<SplatRec>(b, L.rec), tg.tiles_x, tg.tpv, geom->det_w, geom->det_h,
-          uint32_t(L.T), 1, U, thr, log2_tau, 0, nullptr, cnt);
-    else
-      splat_fwd_kernel<true, false, TPB, false><<<grid_for(sunits, TPB), kWave * TPB, 0, s>>>(
-          at<uint2>(b, L.rng), sv, at<SplatRec>(b, L.rec), tg.tiles_x, tg.tpv, geom->det_w, geom->det_h,
-          uint32_t(L.T), 1, U, thr, log2_tau, 0, nullptr, cnt);
-  }, L.K >= kSmallBlockKeysPerTile * L.T);
+  splat_fwd_kernel<true, kSplitNever, 4><<<grid_for(sunits, 4), kWave * 4, 0, s>>>(
+      at<uint2>(b, L.rng), sv, at<SplatRec>(b, L.rec), at<uint32_t>(b, L.kdev), L.R, tg.tiles_x, tg.tpv, geom->det_w,
+      geom->det_h, uint32_t(L.T), 1, U, thr, log2_tau, 0, nullptr, cnt);
   FGS_LAUNCH_CHECK("splat_fwd_kernel<count>");
   return FGS_OK;
 }
