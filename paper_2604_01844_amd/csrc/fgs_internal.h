@@ -20,8 +20,10 @@ namespace fgs {
 // calls (one view, a crop) so that their waves spread over all CUs.
 // A workgroup's LDS is released only when all its waves are done, so a wave
 // that finishes its tile early leaves its slot idle until the workgroup's
-// longest tile ends: the splat kernels take at most 4.
-inline int tiles_per_block(uint64_t n_tiles) { return n_tiles >= 16384 ? 16 : (n_tiles >= 4096 ? 4 : 1); }
+// longest tile ends: the splat kernels take at most 4 (small_blocks).
+inline int tiles_per_block(uint64_t n_tiles, bool small_blocks = false) {
+  return n_tiles >= 16384 ? (small_blocks ? 4 : 16) : (n_tiles >= 4096 ? 4 : 1);
+}
 
 // Waves per tile: a call with few tiles (one view, a crop) splits each
 // tile's list over several waves (strided batches), so that the longest
@@ -83,10 +85,10 @@ __device__ __forceinline__ uint32_t xcd_run_block(uint32_t b, uint32_t n) {
   return r * kRound + (i % kXcds) * kXcdRun + i / kXcds;
 }
 
-// Calls f(std::integral_constant<int, TPB>) with TPB = tiles_per_block(n_tiles).
+// Calls f(std::integral_constant<int, TPB>) with TPB = tiles_per_block(n_tiles, small_blocks).
 template <typename F>
-void with_tiles_per_block(uint64_t n_tiles, F &&f) {
-  switch (tiles_per_block(n_tiles)) {
+void with_tiles_per_block(uint64_t n_tiles, F &&f, bool small_blocks = false) {
+  switch (tiles_per_block(n_tiles, small_blocks)) {
     case 16: f(std::integral_constant<int, 16>()); break;
     case 4: f(std::integral_constant<int, 4>()); break;
     default: f(std::integral_constant<int, 1>()); break;
