@@ -289,6 +289,28 @@ __device__ __forceinline__ void masked_fma8(float (&acc)[8], float w, const floa
 #undef FGS_TERM
 }
 
+// As masked_fma8 for four terms of a backward sum: where arg[k] >= thr,
+// A[k] += G0[k] ex[k], R0 += G0[k] ex[k], R1 += G1[k] ex[k].
+__device__ __forceinline__ void masked_sums4(float (&A)[8], int at, float &R0, float &R1, const float (&G0)[4],
+                                             const float (&G1)[4], const float (&arg)[4], const float (&ex)[4],
+                                             float thr) {
+  uint64_t mask;
+#define FGS_TERM(k, a, x, g, h)          \
+  "v_cmpx_ge_f32 vcc, %" #a ", %23\n\t" \
+  "v_fmac_f32 %" #k ", %" #g ", %" #x "\n\t" \
+  "v_fmac_f32 %4, %" #g ", %" #x "\n\t" \
+  "v_fmac_f32 %5, %" #h ", %" #x "\n\t" \
+  "s_mov_b64 exec, %6\n\t"
+  asm volatile("s_mov_b64 %6, exec\n\t" FGS_TERM(0, 7, 11, 15, 19) FGS_TERM(1, 8, 12, 16, 20)
+                   FGS_TERM(2, 9, 13, 17, 21) FGS_TERM(3, 10, 14, 18, 22)
+               : "+v"(A[at]), "+v"(A[at + 1]), "+v"(A[at + 2]), "+v"(A[at + 3]), "+v"(R0), "+v"(R1), "=&s"(mask)
+               : "v"(arg[0]), "v"(arg[1]), "v"(arg[2]), "v"(arg[3]), "v"(ex[0]), "v"(ex[1]), "v"(ex[2]), "v"(ex[3]),
+                 "v"(G0[0]), "v"(G0[1]), "v"(G0[2]), "v"(G0[3]), "v"(G1[0]), "v"(G1[1]), "v"(G1[2]), "v"(G1[3]),
+                 "v"(thr)
+               : "vcc");
+#undef FGS_TERM
+}
+
 // log2(e): exp(x) = exp2(x * log2(e)). Kernels pre-scale quadratic forms by
 // -log2(e)/2 so that the Gaussian factor is a single v_exp_f32.
 constexpr float kLog2e = 1.4426950408889634f;

@@ -951,7 +951,7 @@ __device__ __forceinline__ float bperm(int src_lane, float v) {
 // round loop spilled, and 72 measured 2% faster on 512^2 views.
 // kTau: the density-aware support, whose per-record threshold the pixel
 // loop reads from LDS; without it the loop compares with the kernel argument.
-template <int TPB, bool kTau>
+template <int TPB>
 __global__ __launch_bounds__(kWave * TPB) __attribute__((amdgpu_waves_per_eu(7, 7))) void splat_bwd_kernel(
     const uint2 *__restrict__ rng, const ListRecs svals,
     const SplatRec *__restrict__ rec, int tiles_x, int tpv, int W, int H, uint32_t n_tiles, int n_chunks,
@@ -1093,15 +1093,14 @@ __global__ __launch_bounds__(kWave * TPB) __attribute__((amdgpu_waves_per_eu(7, 
           const float4 g1 = g4q[kTS * kTS / 4 + row * (kTS / 4) + qd];
           const float G0[4] = {g0.x, g0.y, g0.z, g0.w};
           const float G1[4] = {g1.x, g1.y, g1.z, g1.w};
+          float arg[4], ex[4];
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const float cc = float(qd * 4 + u) - 3.5f;
-            const float arg = fmaf(cc, fmaf(c.x, cc, brow), drow);
-            const float ex = (arg >= (kTau ? c.w : thr)) ? __builtin_amdgcn_exp2f(arg) : 0.f;
-            A[qd * 4 + u] = fmaf(G0[u], ex, A[qd * 4 + u]);
-            R0 = fmaf(G0[u], ex, R0);
-            R1 = fmaf(G1[u], ex, R1);
+            arg[u] = fmaf(cc, fmaf(c.x, cc, brow), drow);
+            ex[u] = __builtin_amdgcn_exp2f(arg[u]);
           }
+          masked_sums4(A, qd * 4, R0, R1, G0, G1, arg, ex, c.w);
         }
         Sr = fmaf(R0, rr, Sr);
         Scr = fmaf(R1, rr, Scr);
@@ -1137,10 +1136,12 @@ __global__ __launch_bounds__(kWave * TPB) __attribute__((amdgpu_waves_per_eu(7, 
         const bool mine = ((mask >> QQ) & 1u) && rel >= 0 && rel < P;
         if (__ballot(mine) == 0ull) continue;
         const int src = mine ? rel : 0;
+        float v[6];
 #pragma unroll
-        for (int k = 0; k < 6; ++k) {
-          const float v = bperm(src, M[k]);
-          tot[k] += mine ? v : 0.f;
+        for (int k = 0; k < 6; ++k) v[k] = bperm(src, M[k]);
+        if (mine) {
+#pragma unroll
+          for (int k = 0; k < 6; ++k) tot[k] += v[k];
         }
       }
       base += P;
@@ -2234,16 +2235,10 @@ extern "C" int fgs_project_views_bwd(const fgs_gaussians *g, const fgs_geom *geo
     const uint64_t units = U.first ? L.n_units : L.T * uint64_t(chunks);
     with_tiles_per_block(units, [&](auto tpb) {
       constexpr int TPB = decltype(tpb)::value;
-      if (opts->density_aabb_tau > 0.f)
-        splat_bwd_kernel<TPB, true><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
-            at<uint2>(b, L.rng), sv, at<SplatRec>(b, L.rec), tg.tiles_x, tg.tpv, geom->det_w, geom->det_h,
-            uint32_t(L.T), chunks, U, thr, log2_tau, (opts->ablate & FGS_ABLATE_QUADRANT_CULL) ? 1 : 0,
-            grad_img, at<float4>(b, L.partials));
-      else
-        splat_bwd_kernel<TPB, false><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
-            at<uint2>(b, L.rng), sv, at<SplatRec>(b, L.rec), tg.tiles_x, tg.tpv, geom->det_w, geom->det_h,
-            uint32_t(L.T), chunks, U, thr, log2_tau, (opts->ablate & FGS_ABLATE_QUADRANT_CULL) ? 1 : 0,
-            grad_img, at<float4>(b, L.partials));
+      splat_bwd_kernel<TPB><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
+          at<uint2>(b, L.rng), sv, at<SplatRec>(b, L.rec), tg.tiles_x, tg.tpv, geom->det_w, geom->det_h,
+          uint32_t(L.T), chunks, U, thr, log2_tau, (opts->ablate & FGS_ABLATE_QUADRANT_CULL) ? 1 : 0, grad_img,
+          at<float4>(b, L.partials));
     }, true);
     FGS_LAUNCH_CHECK("splat_bwd_kernel");
   }
