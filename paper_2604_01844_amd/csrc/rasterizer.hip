@@ -597,22 +597,20 @@ __device__ __forceinline__ void build_quad_lists(uint32_t mask, int lane, uint8_
 // per-pixel exponent, so every pixel keeps the decision of the per-pixel test.
 //
 // Splitting pays when most quadrants are interior, i.e. when Gaussians span
-// many tiles: a call does it when it averages at least kSplitKeysPerRecord
-// tiles per record. A call that read its pair count back knows; at a fixed key
+// many tiles: the forward does it in calls that average at least kSplitForward
+// tiles per record, the backward from kSplitBackward. A call that read its pair count back knows; at a fixed key
 // capacity the kernel reads the count on the device, unless the capacity
 // itself is below the line, so both take the same path for the same pairs.
-// Measured: at 17 tiles per record (sigma 7 pixels) the forward gains a fifth;
-// at 6 (sigma 4) a fifth of the quadrants is interior and the second set of
-// lists costs what it saves.
-constexpr uint64_t kSplitKeysPerRecord = 16;
+// Measured: at 17 tiles per record (sigma 7 pixels) the forward gains a fifth
+// and the backward, whose pixels keep three FMAs each, nothing (3.55 ms whole,
+// 3.60 ms split, 75 views of 512^2); at 180 the backward gains a tenth (22.5
+// against 20.0 ms, 4 views of 2048^2); at 6 (sigma 4) a fifth of the quadrants
+// is interior and the second set of lists costs the forward what it saves.
+constexpr uint64_t kSplitForward = 16, kSplitBackward = 32;
 enum SplitMode { kSplitNever, kSplitAlways, kSplitByCount };
 
-__device__ __forceinline__ bool split_pairs(const uint32_t *__restrict__ kdev, uint64_t n_records) {
-  return uint64_t(kdev[0]) >= kSplitKeysPerRecord * n_records;
-}
-
-inline SplitMode split_mode(uint64_t pairs, uint64_t n_records, bool is_capacity, bool no_cull) {
-  if (no_cull || pairs < kSplitKeysPerRecord * n_records) return kSplitNever;
+inline SplitMode split_mode(uint64_t pairs, uint64_t from, bool is_capacity, bool no_cull) {
+  if (no_cull || pairs < from) return kSplitNever;
   return is_capacity ? kSplitByCount : kSplitAlways;
 }
 
@@ -758,7 +756,7 @@ template <bool kCount, SplitMode kSplit, int TPB>
 __global__ __launch_bounds__(kWave * TPB) __attribute__((amdgpu_waves_per_eu(7, 7))) void splat_fwd_kernel(const uint2 *__restrict__ rng,
                                                            const ListRecs svals,
                                                            const SplatRec *__restrict__ rec,
-                                                           const uint32_t *__restrict__ kdev, uint64_t n_records,
+                                                           const uint32_t *__restrict__ kdev, uint64_t split_from,
                                                            int tiles_x, int tpv, int W, int H,
                                                            uint32_t n_tiles, int n_chunks, Units U, float thr,
                                                            float log2_tau, int no_cull,
@@ -773,7 +771,7 @@ __global__ __launch_bounds__(kWave * TPB) __attribute__((amdgpu_waves_per_eu(7, 
   float4 *s_cw = s_rec_all[wid][0], *s_xy = s_rec_all[wid][1], *s_q = s_rec_all[wid][kArrays / 2],
          *s_e = s_rec_all[wid][kArrays - 2], *s_f = s_rec_all[wid][kArrays - 1];
   uint8_t(*s_list)[kWave] = s_list_all[wid][0], (*s_inner)[kWave] = s_list_all[wid][kLists - 1];
-  const bool split = kSplit == kSplitAlways || (kSplit == kSplitByCount && split_pairs(kdev, n_records));
+  const bool split = kSplit == kSplitAlways || (kSplit == kSplitByCount && uint64_t(kdev[0]) >= split_from);
   const float margin = thr * (kCullSlack - 1.f);
   // work unit: a piece of a tile's list (U.first), or (tile, chunk) where
   // chunk c takes batches c, c + n_chunks, ...; each writes its own partial
@@ -949,12 +947,18 @@ __device__ __forceinline__ float bperm(int src_lane, float v) {
 // the pair's six sums to the pair's emission slot: no atomics, and the
 // summation order is fixed. 72 registers (7 waves per SIMD): at 64 the
 // round loop spilled, and 72 measured 2% faster on 512^2 views.
-// kTau: the density-aware support, whose per-record threshold the pixel
-// loop reads from LDS; without it the loop compares with the kernel argument.
-template <int TPB>
-__global__ __launch_bounds__(kWave * TPB) __attribute__((amdgpu_waves_per_eu(7, 7))) void splat_bwd_kernel(
+// A split call takes the batch's boundary pairs and its interior ones in
+// rounds of their own: an interior row needs two exponentials, and a pixel's
+// factor is a product of the running power p_{k+1} = p_k R and the record's
+// exp2(c00 k^2). Measured, 4 views of 2048^2 and 500,000 Gaussians: 23.4 ms
+// with compare and select per pixel, 22.5 ms with the masked FMAs, 20.0 ms
+// split (80 registers, 6 waves per SIMD).
+template <SplitMode kSplit, int TPB>
+__global__ __launch_bounds__(kWave * TPB)
+    __attribute__((amdgpu_waves_per_eu(kSplit == kSplitNever ? 7 : 6, kSplit == kSplitNever ? 7 : 6)))
+void splat_bwd_kernel(
     const uint2 *__restrict__ rng, const ListRecs svals,
-    const SplatRec *__restrict__ rec, int tiles_x, int tpv, int W, int H, uint32_t n_tiles, int n_chunks,
+    const SplatRec *__restrict__ rec, const uint32_t *__restrict__ kdev, uint64_t split_from, int tiles_x, int tpv, int W, int H, uint32_t n_tiles, int n_chunks,
     Units U, float thr, float log2_tau, int no_cull, const float *__restrict__ gimg,
     float4 *__restrict__ partials) {
   // per pixel: g = dL/dI and g cc (cc: column relative to the quadrant
@@ -963,7 +967,12 @@ __global__ __launch_bounds__(kWave * TPB) __attribute__((amdgpu_waves_per_eu(7, 
   __shared__ float4 s_cw_all[TPB][kWave + 1];
   __shared__ float2 s_xy_all[TPB][kWave + 1];
   __shared__ uint8_t s_cat_all[TPB][4 * kWave];
+  // interior pairs: exp2(c00 k^2), k = 0 .. 7
+  __shared__ float4 s_pow_all[kSplit == kSplitNever ? 1 : TPB][2][kSplit == kSplitNever ? 1 : kWave];
   const int wid = threadIdx.x / kWave;
+  float4 *s_pow = s_pow_all[kSplit == kSplitNever ? 0 : wid][0];
+  const bool split = kSplit == kSplitAlways || (kSplit == kSplitByCount && uint64_t(kdev[0]) >= split_from);
+  const float margin = thr * (kCullSlack - 1.f);
   float4 *s_g4 = s_g4_all[wid][0];
   float *s_g = reinterpret_cast<float *>(s_g4);
   float4 *s_cw = s_cw_all[wid];
@@ -1020,7 +1029,7 @@ __global__ __launch_bounds__(kWave * TPB) __attribute__((amdgpu_waves_per_eu(7, 
   const uint32_t e = b_end;
   for (uint32_t b = b_first; b < e; b += stride) {
     const uint32_t m = min(uint32_t(kWave), e - b);
-    uint32_t mask = 0, slot = 0;
+    uint32_t mask = 0, inner = 0, slot = 0;
     if (uint32_t(lane) < m) {
       const uint32_t r = svals[b + lane];
       const float4 ra = rec[r].a, rb = rec[r].b;
@@ -1031,121 +1040,162 @@ __global__ __launch_bounds__(kWave * TPB) __attribute__((amdgpu_waves_per_eu(7, 
       const float thr_r = support_thr(thr, log2_tau, c.w);
       s_cw[lane] = make_float4(c.x, c.y, c.z, thr_r);
       s_xy[lane] = q;
-      mask = no_cull ? 0xFu : quad_mask(c, q.x, q.y, tx0, ty0, thr_r * kCullSlack);
+      if (split) {
+        const TileForm T = tile_form(c, q.x, q.y, tx0 + 7.5f, ty0 + 7.5f);
+        quad_split(T, c, thr_r, margin, mask, inner);
+        if (inner) {
+          s_pow[lane] = make_float4(1.f, __builtin_amdgcn_exp2f(c.x), __builtin_amdgcn_exp2f(4.f * c.x),
+                                    __builtin_amdgcn_exp2f(9.f * c.x));
+          s_pow[kWave + lane] = make_float4(__builtin_amdgcn_exp2f(16.f * c.x), __builtin_amdgcn_exp2f(25.f * c.x),
+                                            __builtin_amdgcn_exp2f(36.f * c.x), __builtin_amdgcn_exp2f(49.f * c.x));
+        }
+      } else {
+        mask = no_cull ? 0xFu : quad_mask(c, q.x, q.y, tx0, ty0, thr_r * kCullSlack);
+      }
     }
-    // one list of (quadrant << 6 | batch slot) entries, quadrant-major; gpk
-    // holds this lane's record's position in it for each quadrant (8 bits each)
-    int n_pairs = 0;
-    uint32_t gpk = 0;
-#pragma unroll
-    for (int Q = 0; Q < 4; ++Q) {
-      const bool bit = (mask >> Q) & 1u;
-      const uint64_t bal = __ballot(bit);
-      const int gp = n_pairs + __popcll(bal & lt);
-      if (bit) s_cat[gp] = uint8_t((Q << 6) | lane);
-      gpk |= uint32_t(gp & 255) << (8 * Q);
-      n_pairs += __popcll(bal);
-    }
-    wave_lds_sync();
     float tot[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int base = 0; base < n_pairs;) {
-      // a round with at most 32 pairs left spreads each pair's 8 rows over
-      // 2, 4 or 8 lanes (lane = part * P + pair); the parts are summed in a
-      // fixed tree below, so the result stays deterministic
-      const int rem = n_pairs - base;
-      const int lg = rem > 32 ? 0 : rem > 16 ? 1 : rem > 8 ? 2 : 3;
-      const int P = kWave >> lg;
-      const int nrows = 8 >> lg;
-      const int row0 = (lane >> (6 - lg)) * nrows;
-      const float rr0 = float(row0) - 3.5f;
-      const int idx = base + (lane & (P - 1));
-      int Q = 0, j = kWave;
-      if (idx < n_pairs) {
-        const int ent = s_cat[idx];
-        Q = ent >> 6;
-        j = ent & 63;
+    // the batch's boundary pairs, then its interior ones
+    auto rounds = [&](uint32_t mask, auto kind) {
+      constexpr bool kInner = decltype(kind)::value;
+    // one list of (quadrant << 6 | batch slot) entries, quadrant-major; gpk
+      // holds this lane's record's position in it for each quadrant (8 bits each)
+      int n_pairs = 0;
+      uint32_t gpk = 0;
+#pragma unroll
+      for (int Q = 0; Q < 4; ++Q) {
+        const bool bit = (mask >> Q) & 1u;
+        const uint64_t bal = __ballot(bit);
+        const int gp = n_pairs + __popcll(bal & lt);
+        if (bit) s_cat[gp] = uint8_t((Q << 6) | lane);
+        gpk |= uint32_t(gp & 255) << (8 * Q);
+        n_pairs += __popcll(bal);
       }
-      // centre of the pair's quadrant and its first float4 of dL/dI
-      const float ox = float(tx * kTS + (Q & 1) * 8) + 4.f;
-      const float oy = float(ty * kTS + (Q >> 1) * 8) + 4.f;
-      const float4 *g4q = s_g4 + ((Q >> 1) * 8 + row0) * (kTS / 4) + (Q & 1) * 2;
-      const float4 c = s_cw[j];
-      const float2 q = s_xy[j];
-      // Gaussian centre relative to the quadrant centre; arg = c.x dx^2 + c.y dx dy + c.z dy^2
-      const float qx = q.x - ox, qy = q.y - oy;
-      const float m2aqx = -2.f * c.x * qx;
-      const float aqx2 = c.x * qx * qx;
-      const float mbqx = -c.y * qx;
-      // per column: A = sum over rows of g e; per row: sum over columns of
-      // g e and of g e cc, folded into the row moments
-      float A[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      float Sr = 0.f, Scr = 0.f, Srr = 0.f;
+      wave_lds_sync();
+      for (int base = 0; base < n_pairs;) {
+        // a round with at most 32 pairs left spreads each pair's 8 rows over
+        // 2, 4 or 8 lanes (lane = part * P + pair); the parts are summed in a
+        // fixed tree below, so the result stays deterministic
+        const int rem = n_pairs - base;
+        const int lg = rem > 32 ? 0 : rem > 16 ? 1 : rem > 8 ? 2 : 3;
+        const int P = kWave >> lg;
+        const int nrows = 8 >> lg;
+        const int row0 = (lane >> (6 - lg)) * nrows;
+        const float rr0 = float(row0) - 3.5f;
+        const int idx = base + (lane & (P - 1));
+        int Q = 0, j = kWave;
+        if (idx < n_pairs) {
+          const int ent = s_cat[idx];
+          Q = ent >> 6;
+          j = ent & 63;
+        }
+        // centre of the pair's quadrant and its first float4 of dL/dI
+        const float ox = float(tx * kTS + (Q & 1) * 8) + 4.f;
+        const float oy = float(ty * kTS + (Q >> 1) * 8) + 4.f;
+        const float4 *g4q = s_g4 + ((Q >> 1) * 8 + row0) * (kTS / 4) + (Q & 1) * 2;
+        const float4 c = s_cw[j];
+        const float2 q = s_xy[j];
+        // Gaussian centre relative to the quadrant centre; arg = c.x dx^2 + c.y dx dy + c.z dy^2
+        const float qx = q.x - ox, qy = q.y - oy;
+        const float m2aqx = -2.f * c.x * qx;
+        const float aqx2 = c.x * qx * qx;
+        const float mbqx = -c.y * qx;
+        float C[8];
+        if (kInner) {
+          // a lane without a pair (slot kWave) takes slot 0's: its weight below is zero
+          const float4 c0 = s_pow[j & (kWave - 1)], c1 = s_pow[kWave + (j & (kWave - 1))];
+          const float cc[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+#pragma unroll
+          for (int k = 0; k < 8; ++k) C[k] = j == kWave ? 0.f : cc[k];
+        }
+        // per column: A = sum over rows of g e; per row: sum over columns of
+        // g e and of g e cc, folded into the row moments
+        float A[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        float Sr = 0.f, Scr = 0.f, Srr = 0.f;
 #pragma unroll 1
-      for (int row = 0; row < nrows; ++row) {
-        const float rr = rr0 + float(row);
-        const float dy = rr - qy;
-        const float brow = fmaf(c.y, dy, m2aqx);
-        const float drow = fmaf(dy, fmaf(c.z, dy, mbqx), aqx2);
-        float R0 = 0.f, R1 = 0.f;
-#pragma unroll
-        for (int qd = 0; qd < 2; ++qd) {
-          const float4 g0 = g4q[row * (kTS / 4) + qd];
-          const float4 g1 = g4q[kTS * kTS / 4 + row * (kTS / 4) + qd];
-          const float G0[4] = {g0.x, g0.y, g0.z, g0.w};
-          const float G1[4] = {g1.x, g1.y, g1.z, g1.w};
-          float arg[4], ex[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const float cc = float(qd * 4 + u) - 3.5f;
-            arg[u] = fmaf(cc, fmaf(c.x, cc, brow), drow);
-            ex[u] = __builtin_amdgcn_exp2f(arg[u]);
+        for (int row = 0; row < nrows; ++row) {
+          const float rr = rr0 + float(row);
+          const float dy = rr - qy;
+          const float brow = fmaf(c.y, dy, m2aqx);
+          const float drow = fmaf(dy, fmaf(c.z, dy, mbqx), aqx2);
+          float R0 = 0.f, R1 = 0.f, pk = 0.f, R = 0.f;
+          if (kInner) {
+            // the row's first exponent (cc = -3.5) and first step
+            pk = __builtin_amdgcn_exp2f(fmaf(-3.5f, brow, fmaf(12.25f, c.x, drow)));
+            R = __builtin_amdgcn_exp2f(fmaf(-7.f, c.x, brow));
           }
-          masked_sums4(A, qd * 4, R0, R1, G0, G1, arg, ex, c.w);
+#pragma unroll
+          for (int qd = 0; qd < 2; ++qd) {
+            const float4 g0 = g4q[row * (kTS / 4) + qd];
+            const float4 g1 = g4q[kTS * kTS / 4 + row * (kTS / 4) + qd];
+            const float G0[4] = {g0.x, g0.y, g0.z, g0.w};
+            const float G1[4] = {g1.x, g1.y, g1.z, g1.w};
+            if (kInner) {
+#pragma unroll
+              for (int u = 0; u < 4; ++u) {
+                const float ex = pk * C[qd * 4 + u];
+                pk *= R;
+                A[qd * 4 + u] = fmaf(G0[u], ex, A[qd * 4 + u]);
+                R0 = fmaf(G0[u], ex, R0);
+                R1 = fmaf(G1[u], ex, R1);
+              }
+            } else {
+              float arg[4], ex[4];
+#pragma unroll
+              for (int u = 0; u < 4; ++u) {
+                const float cc = float(qd * 4 + u) - 3.5f;
+                arg[u] = fmaf(cc, fmaf(c.x, cc, brow), drow);
+                ex[u] = __builtin_amdgcn_exp2f(arg[u]);
+              }
+              masked_sums4(A, qd * 4, R0, R1, G0, G1, arg, ex, c.w);
+            }
+          }
+          Sr = fmaf(R0, rr, Sr);
+          Scr = fmaf(R1, rr, Scr);
+          Srr = fmaf(R0, rr * rr, Srr);
         }
-        Sr = fmaf(R0, rr, Sr);
-        Scr = fmaf(R1, rr, Scr);
-        Srr = fmaf(R0, rr * rr, Srr);
-      }
-      float S0 = 0.f, Sc = 0.f, Scc = 0.f;
+        float S0 = 0.f, Sc = 0.f, Scc = 0.f;
 #pragma unroll
-      for (int col = 0; col < 8; ++col) {
-        const float cc = float(col) - 3.5f;
-        S0 += A[col];
-        Sc = fmaf(A[col], cc, Sc);
-        Scc = fmaf(A[col], cc * cc, Scc);
-      }
-      // moments about the Gaussian centre: dx = cc - qx, dy = rr - qy
-      float M[6];
-      M[0] = S0;
-      M[1] = fmaf(-qx, S0, Sc);
-      M[2] = fmaf(-qy, S0, Sr);
-      M[3] = fmaf(qx * qx, S0, fmaf(-2.f * qx, Sc, Scc));
-      M[4] = fmaf(qx * qy, S0, fmaf(-qy, Sc, fmaf(-qx, Sr, Scr)));
-      M[5] = fmaf(qy * qy, S0, fmaf(-2.f * qy, Sr, Srr));
-      // parts summed pairwise (halves, then quarters, ...) into lanes < P
-      for (int off = kWave / 2; off >= P; off >>= 1) {
-        const int src = (lane + off) & (kWave - 1);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) M[k] += bperm(src, M[k]);
-      }
-      // the loading lane of each record collects its quadrants' partials from
-      // this round's lanes (quadrants with no pair in the round are skipped)
-#pragma unroll
-      for (int QQ = 0; QQ < 4; ++QQ) {
-        const int rel = int((gpk >> (8 * QQ)) & 255u) - base;
-        const bool mine = ((mask >> QQ) & 1u) && rel >= 0 && rel < P;
-        if (__ballot(mine) == 0ull) continue;
-        const int src = mine ? rel : 0;
-        float v[6];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) v[k] = bperm(src, M[k]);
-        if (mine) {
-#pragma unroll
-          for (int k = 0; k < 6; ++k) tot[k] += v[k];
+        for (int col = 0; col < 8; ++col) {
+          const float cc = float(col) - 3.5f;
+          S0 += A[col];
+          Sc = fmaf(A[col], cc, Sc);
+          Scc = fmaf(A[col], cc * cc, Scc);
         }
+        // moments about the Gaussian centre: dx = cc - qx, dy = rr - qy
+        float M[6];
+        M[0] = S0;
+        M[1] = fmaf(-qx, S0, Sc);
+        M[2] = fmaf(-qy, S0, Sr);
+        M[3] = fmaf(qx * qx, S0, fmaf(-2.f * qx, Sc, Scc));
+        M[4] = fmaf(qx * qy, S0, fmaf(-qy, Sc, fmaf(-qx, Sr, Scr)));
+        M[5] = fmaf(qy * qy, S0, fmaf(-2.f * qy, Sr, Srr));
+        // parts summed pairwise (halves, then quarters, ...) into lanes < P
+        for (int off = kWave / 2; off >= P; off >>= 1) {
+          const int src = (lane + off) & (kWave - 1);
+#pragma unroll
+          for (int k = 0; k < 6; ++k) M[k] += bperm(src, M[k]);
+        }
+        // the loading lane of each record collects its quadrants' partials from
+        // this round's lanes (quadrants with no pair in the round are skipped)
+#pragma unroll
+        for (int QQ = 0; QQ < 4; ++QQ) {
+          const int rel = int((gpk >> (8 * QQ)) & 255u) - base;
+          const bool mine = ((mask >> QQ) & 1u) && rel >= 0 && rel < P;
+          if (__ballot(mine) == 0ull) continue;
+          const int src = mine ? rel : 0;
+          float v[6];
+#pragma unroll
+          for (int k = 0; k < 6; ++k) v[k] = bperm(src, M[k]);
+          if (mine) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) tot[k] += v[k];
+          }
+        }
+        base += P;
       }
-      base += P;
-    }
+    };
+    rounds(mask & ~inner, std::false_type());
+    if (split) rounds(inner, std::true_type());
     if (uint32_t(lane) < m) {
       partials[2 * uint64_t(slot) + 0] = make_float4(tot[0], tot[1], tot[2], tot[3]);
       partials[2 * uint64_t(slot) + 1] = make_float4(tot[4], tot[5], 0.f, 0.f);
@@ -2104,10 +2154,10 @@ extern "C" int fgs_project_views_fwd(const fgs_gaussians *g, const fgs_geom *geo
     auto launch = [&](auto mode, auto tpb) {
       constexpr int TPB = decltype(tpb)::value;
       splat_fwd_kernel<false, decltype(mode)::value, TPB><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
-          at<uint2>(b, L.rng), sv, at<SplatRec>(b, L.rec), at<uint32_t>(b, L.kdev), L.R, tg.tiles_x, tg.tpv,
+          at<uint2>(b, L.rng), sv, at<SplatRec>(b, L.rec), at<uint32_t>(b, L.kdev), kSplitForward * L.R, tg.tiles_x, tg.tpv,
           geom->det_w, geom->det_h, uint32_t(L.T), 1, U, thr, log2_tau, no_cull, part, nullptr);
     };
-    with_split(split_mode(L.K, L.R, ws->key_capacity > 0, no_cull != 0), [&](auto mode) {
+    with_split(split_mode(L.K, kSplitForward * L.R, ws->key_capacity > 0, no_cull != 0), [&](auto mode) {
       if (tiles_per_block(units) > 1)
         launch(mode, std::integral_constant<int, 4>());
       else
@@ -2158,7 +2208,7 @@ extern "C" int fgs_project_views_support(const fgs_gaussians *g, const fgs_geom 
   const Units U = make_units(L, b, use_units(L.T, false));
   const uint64_t sunits = U.first ? L.n_units : L.T;
   splat_fwd_kernel<true, kSplitNever, 4><<<grid_for(sunits, 4), kWave * 4, 0, s>>>(
-      at<uint2>(b, L.rng), sv, at<SplatRec>(b, L.rec), at<uint32_t>(b, L.kdev), L.R, tg.tiles_x, tg.tpv, geom->det_w,
+      at<uint2>(b, L.rng), sv, at<SplatRec>(b, L.rec), at<uint32_t>(b, L.kdev), 0, tg.tiles_x, tg.tpv, geom->det_w,
       geom->det_h, uint32_t(L.T), 1, U, thr, log2_tau, 0, nullptr, cnt);
   FGS_LAUNCH_CHECK("splat_fwd_kernel<count>");
   return FGS_OK;
@@ -2233,13 +2283,20 @@ extern "C" int fgs_project_views_bwd(const fgs_gaussians *g, const fgs_geom *geo
     const Units U = make_units(L, b, use_units(L.T, false));
     const int chunks = U.first ? 1 : chunks_per_tile(L.T);
     const uint64_t units = U.first ? L.n_units : L.T * uint64_t(chunks);
-    with_tiles_per_block(units, [&](auto tpb) {
+    const int no_cull = (opts->ablate & FGS_ABLATE_QUADRANT_CULL) ? 1 : 0;
+    auto launch = [&](auto mode, auto tpb) {
       constexpr int TPB = decltype(tpb)::value;
-      splat_bwd_kernel<TPB><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
-          at<uint2>(b, L.rng), sv, at<SplatRec>(b, L.rec), tg.tiles_x, tg.tpv, geom->det_w, geom->det_h,
-          uint32_t(L.T), chunks, U, thr, log2_tau, (opts->ablate & FGS_ABLATE_QUADRANT_CULL) ? 1 : 0, grad_img,
+      splat_bwd_kernel<decltype(mode)::value, TPB><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
+          at<uint2>(b, L.rng), sv, at<SplatRec>(b, L.rec), at<uint32_t>(b, L.kdev), kSplitBackward * L.R, tg.tiles_x, tg.tpv,
+          geom->det_w, geom->det_h, uint32_t(L.T), chunks, U, thr, log2_tau, no_cull, grad_img,
           at<float4>(b, L.partials));
-    }, true);
+    };
+    with_split(split_mode(L.K, kSplitBackward * L.R, ws->key_capacity > 0, no_cull != 0), [&](auto mode) {
+      if (tiles_per_block(units) > 1)
+        launch(mode, std::integral_constant<int, 4>());
+      else
+        launch(mode, std::integral_constant<int, 1>());
+    });
     FGS_LAUNCH_CHECK("splat_bwd_kernel");
   }
   if (ev) FGS_HIP(hipEventRecord(ev[1], s));

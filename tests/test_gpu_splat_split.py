@@ -1,5 +1,6 @@
 """GPU tests of the rasterizer's split of (quadrant, Gaussian) pairs into
-interior and boundary ones, taken by calls that average 16 tiles or more per
+interior and boundary ones, taken by calls that average 16 (forward) or 32
+(backward) tiles or more per
 Gaussian: both sides of that line, detector edges that cut tiles, single and
 few views (work units) and many, thresholds of large kappa and of the
 density-aware support, and a fixed key capacity."""
@@ -29,6 +30,7 @@ CASES = [
     (40, 0.2, 0.3, 256, 256, 40, "cone", 3.0, 0.0),       # 10,240 tiles: a wave per tile; all but a rim interior
     (60, 0.08, 1.0, 250, 130, 3, "cone", 3.0, 0.0),       # elongated
     (100, 0.06, 0.3, 203, 150, 2, "parallel", 3.0, 0.0),
+    (60, 0.15, 0.3, 203, 150, 2, "cone", 3.0, 0.0),       # 60 tiles each: split in the backward too
     (30, 0.03, 0.2, 256, 256, 1, "cone", 8.0, 0.0),       # threshold -46 in the exponent
     (20, 0.02, 0.2, 512, 512, 1, "cone", 10.0, 0.0),      # threshold -72: never interior
     (300, 0.08, 0.3, 203, 150, 2, "cone", 3.0, 2e-3),
