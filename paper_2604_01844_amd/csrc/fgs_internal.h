@@ -76,13 +76,20 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t n) {
 // As xcd_block, in runs of kXcdRun blocks that the XCDs take in turn: where
 // the work is uneven over the grid (Gaussians in a body, empty tiles around
 // it) every XCD gets its share of it, and neighbours within a run still share
-// an L2. The blocks past the last whole round keep their number.
+// an L2; each round of runs starts one XCD later, so that none keeps to one
+// part of the grid's rows. The blocks past the last whole round keep their number.
 constexpr uint32_t kXcdRun = 16;
 __device__ __forceinline__ uint32_t xcd_run_block(uint32_t b, uint32_t n) {
   constexpr uint32_t kRound = kXcds * kXcdRun;
   const uint32_t r = b / kRound, i = b - r * kRound;
   if ((r + 1u) * kRound > n) return b;
-  return r * kRound + (i % kXcds) * kXcdRun + i / kXcds;
+  return r * kRound + ((i + r) % kXcds) * kXcdRun + i / kXcds;
+}
+
+// The natural order, but each round of eight blocks starts one XCD later.
+__device__ __forceinline__ uint32_t xcd_turn_block(uint32_t b, uint32_t n) {
+  const uint32_t r = b / kXcds;
+  return (r + 1u) * kXcds > n ? b : r * kXcds + (b + r) % kXcds;
 }
 
 // Calls f(std::integral_constant<int, TPB>) with TPB = tiles_per_block(n_tiles, small_blocks).

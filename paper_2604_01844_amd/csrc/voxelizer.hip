@@ -716,8 +716,13 @@ __global__ __launch_bounds__(kWave * TPB) void vox_bwd_kernel(const uint32_t *__
   float *s_g = reinterpret_cast<float *>(s_g4);
   const float h = 0.5f * (kVT - 1);
   // work unit = (tile, chunk): chunk c takes batches c, c + n_chunks, ...
-  // (the natural block order: the XCD-aware one measured 4% slower here)
-  const uint32_t unit = blockIdx.x * TPB + wid;
+  // Natural order: blocks go round the XCDs, so on a wide grid an XCD keeps to
+  // a few columns of tiles and their Gaussians (63.9 ms at 512^3; 67.5 in turned
+  // order, 72.9 with 16 tiles per workgroup). On a row of at most eight blocks
+  // it would keep to one, and with Gaussians in a body the outer XCDs idle (1.31
+  // ms at 256^3), so there each round starts one XCD later (0.97 ms).
+  const uint32_t blk = G.nt[0] <= int(kXcds) * TPB ? xcd_turn_block(blockIdx.x, gridDim.x) : blockIdx.x;
+  const uint32_t unit = blk * TPB + wid;
   if (unit >= n_tiles * uint32_t(n_chunks)) return;
   const uint32_t tile = unit / uint32_t(n_chunks);
   const uint32_t chunk = unit - tile * uint32_t(n_chunks);
@@ -775,14 +780,25 @@ __global__ __launch_bounds__(kWave * TPB) void vox_bwd_kernel(const uint32_t *__
           const float4 g1 = g4[kVT * kVT * kVT / 4 + qd];
           const float G0[4] = {g0.x, g0.y, g0.z, g0.w};
           const float G1[4] = {g1.x, g1.y, g1.z, g1.w};
+          float arg[4], ex[4];
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const float cx = float(qd * 4 + u) - h;
-            const float arg = fmaf(cx, fmaf(c0.x, cx, brow), drow);
-            const float ex = (arg >= c1.z) ? __builtin_amdgcn_exp2f(arg) : 0.f;
-            A[qd * 4 + u] = fmaf(G0[u], ex, A[qd * 4 + u]);
-            R0 = fmaf(G0[u], ex, R0);
-            R1 = fmaf(G1[u], ex, R1);
+            arg[u] = fmaf(cx, fmaf(c0.x, cx, brow), drow);
+            ex[u] = __builtin_amdgcn_exp2f(arg[u]);
+          }
+          // (a call of few waves waits on the mask instead of on issue slots: 18.0
+          // against 19.5 us for a 32^3 crop)
+          if (TPB > 1) {
+            masked_sums4(A, qd * 4, R0, R1, G0, G1, arg, ex, c1.z);
+          } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const float e = (arg[u] >= c1.z) ? ex[u] : 0.f;
+              A[qd * 4 + u] = fmaf(G0[u], e, A[qd * 4 + u]);
+              R0 = fmaf(G0[u], e, R0);
+              R1 = fmaf(G1[u], e, R1);
+            }
           }
         }
         Sy = fmaf(R0, cy, Sy);
@@ -1239,7 +1255,7 @@ int vox_backward(const fgs_gaussians *g, const fgs_grid *grid, const fgs_opts *o
     const int chunks = chunks_per_tile(L.T);
     const uint64_t units = L.T * uint64_t(chunks);
     with_tiles_per_block(units, [&](auto tpb) {
-      constexpr int TPB = decltype(tpb)::value;
+      constexpr int TPB = decltype(tpb)::value > 4 ? 4 : decltype(tpb)::value;
       vox_bwd_kernel<TPB><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
           at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
           at<uint32_t>(b, L.gid), G, uint32_t(L.T), chunks, grad_vol, at<float2>(b, L.partials));
