@@ -150,38 +150,58 @@ __global__ __launch_bounds__(256) void vox_record_kernel(fgs_gaussians g, GridDe
 // over the box lo <= p + d <= hi. Its maximiser lies on one of the three
 // planes x_a = clamp(p_a); on each, the restricted 2D form is maximised over
 // the face rectangle along its two clamped lines (the same construction as
-// the rasterizer's quadrant test, one dimension up).
-__device__ float box_qmax(const float4 &c0, const float4 &c1, const float p[3], const float lo[3],
-                          const float hi[3]) {
-  const float M[3][3] = {{c0.x, 0.5f * c0.y, 0.5f * c0.z},
-                         {0.5f * c0.y, c0.w, 0.5f * c1.x},
-                         {0.5f * c0.z, 0.5f * c1.x, c1.y}};
-  float best = -INFINITY;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const int b = (a + 1) % 3, c = (a + 2) % 3;
-    const float D = fminf(fmaxf(p[a], lo[a]), hi[a]) - p[a];
-    const float lb = lo[b] - p[b], hb = hi[b] - p[b], lc = lo[c] - p[c], hc = hi[c] - p[c];
-    const float mbb = M[b][b], mcc = M[c][c], mbc = M[b][c], mab = M[a][b], mac = M[a][c];
-    const float det = mbb * mcc - mbc * mbc;
-    if (!(det > 0.f)) return 0.f;  // degenerate form: keep the tile
-    const float ybh = -D * (mcc * mab - mbc * mac) / det;
-    const float ych = -D * (mbb * mac - mbc * mab) / det;
-    const float yb1 = fminf(fmaxf(ybh, lb), hb);
-    const float yc1 = fminf(fmaxf(-(mbc * yb1 + D * mac) / mcc, lc), hc);
-    const float yc2 = fminf(fmaxf(ych, lc), hc);
-    const float yb2 = fminf(fmaxf(-(mbc * yc2 + D * mab) / mbb, lb), hb);
-    const float base = M[a][a] * D * D;
-    const float f1 = base + 2.f * D * (mab * yb1 + mac * yc1) + yb1 * (mbb * yb1 + 2.f * mbc * yc1) + mcc * yc1 * yc1;
-    const float f2 = base + 2.f * D * (mab * yb2 + mac * yc2) + yb2 * (mbb * yb2 + 2.f * mbc * yc2) + mcc * yc2 * yc2;
-    best = fmaxf(best, fmaxf(f1, f2));
-  }
-  return best;
-}
+// the rasterizer's quadrant test, one dimension up). The quotients that do not
+// depend on the box are taken once per Gaussian.
+struct BoxTest {
+  float M[3][3];
+  float kb[3], kc[3];  // maximiser of plane a's 2D form per unit of D, negated
+  float inv[3];        // 1 / M[a][a]
+  bool degenerate;     // a 2 x 2 minor is not positive: every box counts as reached
 
-// Tile j (row-major, x fastest) of rectangle rc, and whether the Gaussian's
-// support ellipsoid reaches one of its voxel centres (a superset test: the
-// threshold carries a small slack).
+  __device__ __forceinline__ BoxTest(const float4 &c0, const float4 &c1)
+      : M{{c0.x, 0.5f * c0.y, 0.5f * c0.z}, {0.5f * c0.y, c0.w, 0.5f * c1.x}, {0.5f * c0.z, 0.5f * c1.x, c1.y}} {
+    degenerate = false;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const int b = (a + 1) % 3, c = (a + 2) % 3;
+      const float det = M[b][b] * M[c][c] - M[b][c] * M[b][c];
+      degenerate |= !(det > 0.f);
+      const float id = 1.f / det;
+      kb[a] = (M[c][c] * M[a][b] - M[b][c] * M[a][c]) * id;
+      kc[a] = (M[b][b] * M[a][c] - M[b][c] * M[a][b]) * id;
+      inv[a] = 1.f / M[a][a];
+    }
+  }
+
+  // d0: the box's lower corner less the Gaussian's centre; side: its side
+  __device__ __forceinline__ float qmax(const float (&d0)[3], float side) const {
+    float best = -INFINITY;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const int b = (a + 1) % 3, c = (a + 2) % 3;
+      const float D = fminf(fmaxf(0.f, d0[a]), d0[a] + side);
+      const float lb = d0[b], hb = d0[b] + side, lc = d0[c], hc = d0[c] + side;
+      const float yb1 = fminf(fmaxf(-D * kb[a], lb), hb);
+      const float yc1 = fminf(fmaxf(-fmaf(M[b][c], yb1, D * M[a][c]) * inv[c], lc), hc);
+      const float yc2 = fminf(fmaxf(-D * kc[a], lc), hc);
+      const float yb2 = fminf(fmaxf(-fmaf(M[b][c], yc2, D * M[a][b]) * inv[b], lb), hb);
+      const float f1 = fmaf(M[a][a] * D, D, fmaf(2.f * D, fmaf(M[a][b], yb1, M[a][c] * yc1),
+                            fmaf(yb1, fmaf(M[b][b], yb1, 2.f * M[b][c] * yc1), M[c][c] * yc1 * yc1)));
+      const float f2 = fmaf(M[a][a] * D, D, fmaf(2.f * D, fmaf(M[a][b], yb2, M[a][c] * yc2),
+                            fmaf(yb2, fmaf(M[b][b], yb2, 2.f * M[b][c] * yc2), M[c][c] * yc2 * yc2)));
+      best = fmaxf(best, fmaxf(f1, f2));
+    }
+    return best;
+  }
+
+  // Whether the support reaches one of the voxel centres of tile (tx, ty, tz),
+  // as far as the culling threshold says (a superset test).
+  __device__ __forceinline__ bool hit(const float4 &p, uint32_t tx, uint32_t ty, uint32_t tz, float thr_cull) const {
+    const float d0[3] = {float(tx * kVT) - p.x, float(ty * kVT) - p.y, float(tz * kVT) - p.z};
+    return degenerate || qmax(d0, float(kVT - 1)) >= thr_cull;
+  }
+};
+
 // Tile j of the rectangle, row-major (x fastest).
 __device__ __forceinline__ void tile_coords(const Rect3 &rc, uint32_t j, uint32_t &tx, uint32_t &ty, uint32_t &tz) {
   const uint32_t nx = uint32_t(rc.v[3]) - rc.v[0] + 1u, ny = uint32_t(rc.v[4]) - rc.v[1] + 1u;
@@ -191,16 +211,6 @@ __device__ __forceinline__ void tile_coords(const Rect3 &rc, uint32_t j, uint32_
   tx = rc.v[0] + (jxy - jy * nx);
   ty = rc.v[1] + jy;
   tz = rc.v[2] + jz;
-}
-
-__device__ __forceinline__ bool tile_hit(const Rect3 &rc, uint32_t j, const float4 &p, const float4 &c0,
-                                         const float4 &c1, float thr_cull, uint32_t &tx, uint32_t &ty,
-                                         uint32_t &tz) {
-  tile_coords(rc, j, tx, ty, tz);
-  const float pc[3] = {p.x, p.y, p.z};
-  const float lo[3] = {float(tx * kVT), float(ty * kVT), float(tz * kVT)};
-  const float hi[3] = {lo[0] + float(kVT - 1), lo[1] + float(kVT - 1), lo[2] + float(kVT - 1)};
-  return box_qmax(c0, c1, pc, lo, hi) >= thr_cull;
 }
 
 __device__ __forceinline__ uint32_t rect_tiles(const Rect3 &rc) {
@@ -243,7 +253,7 @@ struct TileWalk {
 };
 
 // Hits among tiles [j0, j0 + n) of the rectangle, n <= kHitTiles, as ballots
-// words[] in LDS (bit i of words[g]: tile j0 + 64 g + i): tile_hit's decisions.
+// words[] in LDS (bit i of words[g]: tile j0 + 64 g + i): BoxTest's decisions.
 // Most tiles need no exact test: the tangent at the tile's centre bounds the
 // form over the tile from above (missed), its value at the tile's point
 // nearest the centre of the Gaussian from below (hit); both with a margin of
@@ -252,16 +262,14 @@ struct TileWalk {
 // 64 at a time. A form whose 2 x 2 minors are not positive keeps every tile,
 // as the exact test does. 500,000 Gaussians at 512^3 (1,900 tiles per
 // rectangle): count and emission 8.9 + 8.5 ms with an exact test per tile,
-// TIMEC now.
+// 2.1 + 3.3 ms now (the keys written are 6.6 GB).
 __device__ __forceinline__ void chunk_hits(const Rect3 &rc, uint32_t j0, uint32_t n, const float4 &p, const float4 &c0,
                                            const float4 &c1, float thr_cull, int lane,
                                            unsigned long long *__restrict__ words,
                                            unsigned short *__restrict__ unsure) {
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   const float h = 0.5f * (kVT - 1);
-  const float m01 = 0.5f * c0.y, m02 = 0.5f * c0.z, m12 = 0.5f * c1.x;
-  const bool degenerate = !(c0.w * c1.y - m12 * m12 > 0.f) || !(c1.y * c0.x - m02 * m02 > 0.f) ||
-                          !(c0.x * c0.w - m01 * m01 > 0.f);
+  const BoxTest box(c0, c1);
   const float size = fabsf(c0.x) + fabsf(c0.y) + fabsf(c0.z) + fabsf(c0.w) + fabsf(c1.x) + fabsf(c1.y);
   TileWalk w(rc, j0 + uint32_t(lane));
   uint32_t n_unsure = 0;
@@ -283,7 +291,7 @@ __device__ __forceinline__ void chunk_hits(const Rect3 &rc, uint32_t j0, uint32_
       const float ex = dx + nx, ey = dy + ny, ez = dz + nz;
       const float near = fmaf(ex, fmaf(c0.x, ex, fmaf(c0.y, ey, c0.z * ez)),
                               fmaf(ey, fmaf(c0.w, ey, c1.x * ez), c1.y * ez * ez));
-      hit = degenerate || near >= thr_cull + margin;
+      hit = box.degenerate || near >= thr_cull + margin;
       open = !hit && !(fmaf(h, fabsf(gx) + fabsf(gy) + fabsf(gz), q) < thr_cull - margin);
     }
     const uint64_t bal = __ballot(hit), amb = __ballot(open);
@@ -297,14 +305,22 @@ __device__ __forceinline__ void chunk_hits(const Rect3 &rc, uint32_t j0, uint32_
     if (r + uint32_t(lane) < n_unsure) {
       const uint32_t i = unsure[r + lane];
       uint32_t tx, ty, tz;
-      if (tile_hit(rc, j0 + i, p, c0, c1, thr_cull, tx, ty, tz)) atomicOr(&words[i >> 6], 1ull << (i & 63u));
+      tile_coords(rc, j0 + i, tx, ty, tz);
+      if (box.hit(p, tx, ty, tz, thr_cull)) atomicOr(&words[i >> 6], 1ull << (i & 63u));
     }
   }
   wave_lds_sync();
 }
 
-// One wave per Gaussian: the number of tiles of its rectangle that its
-// support reaches (the key count).
+// A wave takes four Gaussians. Rectangles of at most 64 tiles are walked by 16
+// lanes each, all four at once; larger ones by the whole wave, one after the
+// other (200,000 Gaussians of 30-odd tiles at 256^3: 140 us with a wave per
+// Gaussian, 75 us now).
+constexpr int kWaveGauss = 4;
+constexpr uint32_t kSmallTiles = 64;
+
+// The number of tiles of each Gaussian's rectangle that its support reaches
+// (the key count).
 __global__ __launch_bounds__(256) void vox_count_kernel(int64_t n, const float4 *__restrict__ prho,
                                                         const float4 *__restrict__ a0,
                                                         const float4 *__restrict__ a1,
@@ -314,17 +330,54 @@ __global__ __launch_bounds__(256) void vox_count_kernel(int64_t n, const float4 
   __shared__ unsigned long long s_words[4][kHitWords];
   __shared__ unsigned short s_unsure[4][kHitTiles];
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t i = int64_t(blockIdx.x) * 4 + wid;
-  if (i >= n) return;
-  const Rect3 rc = rect[i];
-  const uint32_t nt = rect_tiles(rc);
-  uint32_t cnt = 0;
-  if (nt) {
+  const int64_t i0 = (int64_t(blockIdx.x) * 4 + wid) * kWaveGauss;
+  if (i0 >= n) return;
+  const int grp = lane >> 4, l16 = lane & 15;
+  {
+    const int64_t i = i0 + grp;
+    Rect3 rc{};
+    uint32_t nt = 0;
+    if (i < n) {
+      rc = rect[i];
+      nt = rect_tiles(rc);
+    }
+    const uint32_t small = nt <= kSmallTiles ? nt : 0u;
+    unsigned long long word = 0;
+    if (__ballot(small != 0u)) {
+      float4 p = make_float4(0.f, 0.f, 0.f, 0.f), c0 = p, c1 = p;
+      if (small) {
+        p = prho[i];
+        c0 = a0[i];
+        c1 = a1[i];
+      }
+      const BoxTest box(c0, c1);
+      const float thr_cull = c1.z + thr_widen;
+      for (uint32_t r = 0; __ballot(r < small); r += 16) {
+        bool hit = false;
+        if (r + uint32_t(l16) < small) {
+          uint32_t tx, ty, tz;
+          tile_coords(rc, r + uint32_t(l16), tx, ty, tz);
+          hit = box.hit(p, tx, ty, tz, thr_cull);
+        }
+        word |= ((__ballot(hit) >> (16 * grp)) & 0xffffull) << r;
+      }
+    }
+    if (i < n && l16 == 0 && nt <= kSmallTiles) {
+      if (nt) hits[uint64_t(i) * kHitWords] = word;
+      count[i] = uint32_t(__popcll(word));
+    }
+  }
+  for (int g = 0; g < kWaveGauss; ++g) {
+    const int64_t i = i0 + g;
+    if (i >= n) break;
+    const Rect3 rc = rect[i];
+    const uint32_t nt = rect_tiles(rc);
+    if (nt <= kSmallTiles) continue;
+    uint32_t cnt = 0;
     const float4 p = prho[i], c0 = a0[i], c1 = a1[i];
-    const float thr_cull = c1.z + thr_widen;
     for (uint32_t j0 = 0; j0 < nt; j0 += kHitTiles) {
       const uint32_t m = min(uint32_t(kHitTiles), nt - j0);
-      chunk_hits(rc, j0, m, p, c0, c1, thr_cull, lane, s_words[wid], s_unsure[wid]);
+      chunk_hits(rc, j0, m, p, c0, c1, c1.z + thr_widen, lane, s_words[wid], s_unsure[wid]);
       const unsigned long long wd = uint32_t(lane) * 64u < m ? s_words[wid][lane & (kHitWords - 1)] : 0ull;
       if (nt <= uint32_t(kHitTiles) && uint32_t(lane) * 64u < m) hits[uint64_t(i) * kHitWords + lane] = wd;
       uint32_t c = uint32_t(__popcll(wd));
@@ -333,14 +386,14 @@ __global__ __launch_bounds__(256) void vox_count_kernel(int64_t n, const float4 
       cnt += uint32_t(__builtin_amdgcn_readfirstlane(int(c)));
       wave_lds_sync();
     }
+    if (lane == 0) count[i] = cnt;
   }
-  if (lane == 0) count[i] = cnt;
 }
 
-// One wave per Gaussian: the keys of the tiles its support reaches, in
-// row-major order, at its offset. The sort's value is the emission slot q
-// (a Gaussian's slots are contiguous, which is where the backward writes its
-// partial sums); gid[q] is the Gaussian.
+// The keys of the tiles that each Gaussian's support reaches, in row-major
+// order, at its offset. The sort's value is the emission slot q (a Gaussian's
+// slots are contiguous, which is where the backward writes its partial sums);
+// gid[q] is the Gaussian.
 __global__ __launch_bounds__(256) void vox_emit_kernel(int64_t n, int ntx, int nty, const float4 *__restrict__ prho,
                                                        const float4 *__restrict__ a0,
                                                        const float4 *__restrict__ a1,
@@ -354,33 +407,62 @@ __global__ __launch_bounds__(256) void vox_emit_kernel(int64_t n, int ntx, int n
   __shared__ unsigned long long s_words[4][kHitWords];
   __shared__ unsigned short s_unsure[4][kHitTiles];
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t i = int64_t(blockIdx.x) * 4 + wid;
-  if (i >= n) return;
-  uint32_t o = offset[i];
-  if (o == offset[i + 1]) return;
-  const Rect3 rc = rect[i];
-  const uint32_t nt = rect_tiles(rc);
-  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  const bool stored = nt <= uint32_t(kHitTiles);  // the count kept this rectangle's ballots
-  TileWalk w(rc, uint32_t(lane));
-  for (uint32_t j0 = 0; j0 < nt; j0 += kHitTiles) {
-    const uint32_t m = min(uint32_t(kHitTiles), nt - j0);
-    if (!stored) {
-      const float4 p = prho[i], c0 = a0[i], c1 = a1[i];
-      chunk_hits(rc, j0, m, p, c0, c1, c1.z + thr_widen, lane, s_words[wid], s_unsure[wid]);
-    }
-    for (uint32_t g = 0; g * 64u < m; ++g) {
-      const uint64_t bal = stored ? hits[uint64_t(i) * kHitWords + g] : s_words[wid][g];
-      if ((bal >> lane) & 1ull) {
-        const uint32_t q = o + uint32_t(__popcll(bal & lt));
-        keys[q] = ((w.z + rc.v[2]) * uint32_t(nty) + w.y + rc.v[1]) * uint32_t(ntx) + w.x + rc.v[0];
-        vals[q] = q;
-        gid[q] = uint32_t(i);
+  const int64_t i0 = (int64_t(blockIdx.x) * 4 + wid) * kWaveGauss;
+  if (i0 >= n) return;
+  const int grp = lane >> 4, l16 = lane & 15;
+  auto put = [&](uint32_t q, uint32_t tx, uint32_t ty, uint32_t tz, int64_t i) {
+    keys[q] = (tz * uint32_t(nty) + ty) * uint32_t(ntx) + tx;
+    vals[q] = q;
+    gid[q] = uint32_t(i);
+  };
+  {
+    const int64_t i = i0 + grp;
+    unsigned long long word = 0;
+    uint32_t o = 0;
+    Rect3 rc{};
+    if (i < n) {
+      o = offset[i];
+      if (offset[i + 1] != o) {
+        rc = rect[i];
+        if (rect_tiles(rc) <= kSmallTiles) word = hits[uint64_t(i) * kHitWords];
       }
-      o += uint32_t(__popcll(bal));
-      w.next();
     }
-    wave_lds_sync();
+    for (uint32_t r = 0; __ballot(word >> r != 0ull); r += 16) {
+      const uint32_t j = r + uint32_t(l16);
+      if ((word >> j) & 1ull) {
+        uint32_t tx, ty, tz;
+        tile_coords(rc, j, tx, ty, tz);
+        put(o + uint32_t(__popcll(word & ((1ull << j) - 1ull))), tx, ty, tz, i);
+      }
+      if (r == 48) break;
+    }
+  }
+  for (int g = 0; g < kWaveGauss; ++g) {
+    const int64_t i = i0 + g;
+    if (i >= n) break;
+    uint32_t o = offset[i];
+    if (o == offset[i + 1]) continue;
+    const Rect3 rc = rect[i];
+    const uint32_t nt = rect_tiles(rc);
+    if (nt <= kSmallTiles) continue;
+    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    const bool stored = nt <= uint32_t(kHitTiles);  // the count kept this rectangle's ballots
+    TileWalk w(rc, uint32_t(lane));
+    for (uint32_t j0 = 0; j0 < nt; j0 += kHitTiles) {
+      const uint32_t m = min(uint32_t(kHitTiles), nt - j0);
+      if (!stored) {
+        const float4 p = prho[i], c0 = a0[i], c1 = a1[i];
+        chunk_hits(rc, j0, m, p, c0, c1, c1.z + thr_widen, lane, s_words[wid], s_unsure[wid]);
+      }
+      for (uint32_t gw = 0; gw * 64u < m; ++gw) {
+        const uint64_t bal = stored ? hits[uint64_t(i) * kHitWords + gw] : s_words[wid][gw];
+        if ((bal >> lane) & 1ull)
+          put(o + uint32_t(__popcll(bal & lt)), w.x + rc.v[0], w.y + rc.v[1], w.z + rc.v[2], i);
+        o += uint32_t(__popcll(bal));
+        w.next();
+      }
+      wave_lds_sync();
+    }
   }
 }
 
@@ -392,7 +474,7 @@ __global__ __launch_bounds__(256) void vox_ranges_kernel(const uint32_t *__restr
   // A thread writes the starts of the tiles between its key's and the previous
   // one's; a long run of empty tiles (the margins of a grid) is filled by the
   // whole wave (200,000 Gaussians in the middle of 256^3: 145 us with a thread
-  // per run, TIMER now).
+  // per run, 10 us now).
   int64_t prev = 0, cur = 0;
   if (k <= K) {
     prev = (k == 0) ? -1 : int64_t(skeys[k - 1]);
@@ -1381,7 +1463,7 @@ int vox_build(const fgs_gaussians *g, const fgs_grid *grid, const fgs_opts *o, f
                                                       at<Rect3>(b, L.rect));
   FGS_LAUNCH_CHECK("vox_record_kernel");
   const float thr_widen = cull_widening(o);
-  vox_count_kernel<<<grid_for(N, 4), 256, 0, s>>>(int64_t(N), at<float4>(b, L.prho), at<float4>(b, L.a0),
+  vox_count_kernel<<<grid_for(N, 4 * kWaveGauss), 256, 0, s>>>(int64_t(N), at<float4>(b, L.prho), at<float4>(b, L.a0),
                                                    at<float4>(b, L.a1), at<Rect3>(b, L.rect), thr_widen,
                                                    at<uint32_t>(b, L.offset), at<unsigned long long>(b, L.hits));
   FGS_LAUNCH_CHECK("vox_count_kernel");
@@ -1407,7 +1489,7 @@ int vox_build(const fgs_gaussians *g, const fgs_grid *grid, const fgs_opts *o, f
   }
   const uint64_t K = L.K;
   if (K > 0) {
-    vox_emit_kernel<<<grid_for(N, 4), 256, 0, s>>>(int64_t(N), G.nt[0], G.nt[1], at<float4>(b, L.prho),
+    vox_emit_kernel<<<grid_for(N, 4 * kWaveGauss), 256, 0, s>>>(int64_t(N), G.nt[0], G.nt[1], at<float4>(b, L.prho),
                                                     at<float4>(b, L.a0), at<float4>(b, L.a1), at<Rect3>(b, L.rect),
                                                     thr_widen, at<uint32_t>(b, L.offset),
                                                     at<unsigned long long>(b, L.hits), at<uint32_t>(b, L.keys),
