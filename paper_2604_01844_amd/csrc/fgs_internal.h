@@ -86,10 +86,16 @@ __device__ __forceinline__ uint32_t xcd_run_block(uint32_t b, uint32_t n) {
   return r * kRound + ((i + r) % kXcds) * kXcdRun + i / kXcds;
 }
 
-// The natural order, but each round of eight blocks starts one XCD later.
-__device__ __forceinline__ uint32_t xcd_turn_block(uint32_t b, uint32_t n) {
-  const uint32_t r = b / kXcds;
-  return (r + 1u) * kXcds > n ? b : r * kXcds + (b + r) % kXcds;
+// The natural order, but each 32 blocks are turned by 9 more places than the 32
+// before them. Blocks go round the XCDs, and inside an XCD round its four
+// shader engines, without regard to their load: where a row of the grid is 8 or
+// 32 blocks, an XCD or an engine would keep to one part of every row, and with
+// Gaussians in a body the outer parts are empty. The last, partial 32 keep
+// their number.
+__device__ __forceinline__ uint32_t turned_block(uint32_t b, uint32_t n) {
+  constexpr uint32_t kRound = kXcds * 4;
+  const uint32_t r = b / kRound;
+  return (r + 1u) * kRound > n ? b : r * kRound + (b + 9u * r) % kRound;
 }
 
 // Calls f(std::integral_constant<int, TPB>) with TPB = tiles_per_block(n_tiles, small_blocks).

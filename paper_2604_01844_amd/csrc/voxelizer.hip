@@ -934,11 +934,9 @@ __global__ __launch_bounds__(kWave * TPB) void vox_bwd_kernel(const uint32_t *__
   const float h = 0.5f * (kVT - 1);
   // work unit = (tile, chunk): chunk c takes batches c, c + n_chunks, ...
   // Natural order: blocks go round the XCDs, so on a wide grid an XCD keeps to
-  // a few columns of tiles and their Gaussians (63.9 ms at 512^3; 67.5 in turned
-  // order, 72.9 with 16 tiles per workgroup). On a row of at most eight blocks
-  // it would keep to one, and with Gaussians in a body the outer XCDs idle (1.31
-  // ms at 256^3), so there each round starts one XCD later (0.97 ms).
-  const uint32_t blk = G.nt[0] <= int(kXcds) * TPB ? xcd_turn_block(blockIdx.x, gridDim.x) : blockIdx.x;
+  // a few columns of tiles and their Gaussians (63.9 ms at 512^3 against 67.5
+  // in turned order); on a narrow one the turned order keeps the load even.
+  const uint32_t blk = G.nt[0] <= int(kXcds) * 4 ? turned_block(blockIdx.x, gridDim.x) : blockIdx.x;
   const uint32_t unit = blk * TPB + wid;
   if (unit >= n_tiles * uint32_t(n_chunks)) return;
   const uint32_t tile = unit / uint32_t(n_chunks);
@@ -1168,7 +1166,7 @@ __global__ __launch_bounds__(kWave * TPB) __attribute__((amdgpu_waves_per_eu(5, 
   float *s_g = reinterpret_cast<float *>(s_g4);
   uint32_t(*s_ring)[2 * kWave] = s_ring_all[wid];
   const float h = 0.5f * (kVT - 1);
-  const uint32_t blk = G.nt[0] <= int(kXcds) * TPB ? xcd_turn_block(blockIdx.x, gridDim.x) : blockIdx.x;
+  const uint32_t blk = G.nt[0] <= int(kXcds) * TPB ? turned_block(blockIdx.x, gridDim.x) : blockIdx.x;
   const uint32_t tile = blk * TPB + wid;
   if (tile >= n_tiles) return;
   const int tx = int(tile % uint32_t(G.nt[0]));
@@ -1395,6 +1393,16 @@ float cull_widening(const fgs_opts *o) { return -0.5f * kLog2e * o->kappa * o->k
 // tiles per Gaussian (at a fixed key capacity the count is not known here).
 bool many_keys(const fgs_workspace *ws, const VoxLayout &L) {
   return ws->key_capacity == 0 && L.K >= kProductKeysPerRecord * L.N;
+}
+
+// Waves per tile in the backward, whose pairs are independent of each other:
+// as in the forward, but four also where lists average two batches of 64 or
+// more. A wave per tile leaves the longest lists to the end: 200,000 Gaussians
+// in the middle of 256^3, lists of some 500 to 800 in a fifth of the tiles: 0.79 ms
+// with one, 0.56 ms with four (the CUs busy 58% and 93% of the time).
+int backward_chunks(const fgs_workspace *ws, const VoxLayout &L) {
+  const int c = chunks_per_tile(L.T);
+  return c == 1 && ws->key_capacity == 0 && L.K >= kWave * L.T ? 4 : c;
 }
 
 template <typename T>
@@ -1662,9 +1670,9 @@ int vox_backward(const fgs_gaussians *g, const fgs_grid *grid, const fgs_opts *o
   hipEvent_t *ev = static_cast<hipEvent_t *>(opts->events);
   if (ev) FGS_HIP(hipEventRecord(ev[0], s));
   if (L.K > 0) {
-    const int chunks = chunks_per_tile(L.T);
+    const int chunks = backward_chunks(ws, L);
     const uint64_t units = L.T * uint64_t(chunks);
-    if (chunks == 1 && many_keys(ws, L)) {
+    if (chunks_per_tile(L.T) == 1 && many_keys(ws, L)) {
       vox_bwd_product_kernel<4><<<grid_for(L.T, 4), kWave * 4, 0, s>>>(
           at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
           at<uint32_t>(b, L.gid), G, uint32_t(L.T), cull_widening(opts), grad_vol, at<float2>(b, L.partials));
