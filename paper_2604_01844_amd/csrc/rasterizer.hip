@@ -1456,24 +1456,52 @@ struct ExactCam {
   float fu, fv, cu, cv, k2;
 };
 
-template <bool kCount, int TPB>
-__global__ __launch_bounds__(kWave * TPB) void splat_fwd_exact_kernel(
+// Four waves share a tile (or, with few tiles, each of its chunks): they take
+// the batches of its list in turn. Lists are uneven (50,000 Gaussians of sigma
+// 0.03 at 512 x 512: up to some 2,000 in the body's tiles, none around it) and
+// these kernels issue little else than arithmetic, so with a wave per list the
+// longest ones and the CUs that held them ended last: CUs busy 44% (forward) and 59%
+// (backward) of the time over 4 views; forward and backward with their binning
+// 1.67 -> 1.09 ms, over 16 views 5.3 -> 3.7 ms.
+constexpr int kExactWaves = 4;
+
+// Blocks of the ray-exact kernels; rows of blocks keep the work-items of each
+// dimension below 2^32.
+inline dim3 exact_blocks(uint64_t units) {
+  constexpr uint64_t kRow = 1u << 22;
+  return units <= kRow ? dim3(unsigned(units)) : dim3(unsigned(kRow), grid_for(units, unsigned(kRow)));
+}
+// Their order: from four views on each XCD takes an eighth of the tiles, half
+// a view or more, and its L2 keeps their records (8 views of 600 x 600: 2.50 ms, 2.72 in
+// the natural order); below that an eighth is a few rows of one view, empty
+// for the outer XCDs, and the natural order shares the work (1 view of 512 x 512: 0.39 ms,
+// 0.54 by eighths; 2 of 256 x 256: 0.30 and 0.38).
+__device__ __forceinline__ uint64_t exact_unit(uint32_t views) {
+  return uint64_t(blockIdx.y) * gridDim.x +
+         (views >= 4 ? xcd_turned_block(blockIdx.x, gridDim.x) : turned_block(blockIdx.x, gridDim.x));
+}
+
+// The waves' sums meet in LDS in a fixed order; wave k writes pixel row k.
+template <bool kCount>
+__global__ __launch_bounds__(kWave * kExactWaves) void splat_fwd_exact_kernel(
     const uint2 *__restrict__ rng, const ListRecs svals, const ExactRec *__restrict__ rec,
     int tiles_x, int tpv, int W, int H, uint32_t n_tiles, int n_chunks, float thr, float thr_cull, ExactCam cam,
     float *__restrict__ img, unsigned long long *__restrict__ counter) {
-  __shared__ float4 s_a_all[TPB][kWave + 1];
-  __shared__ float4 s_b_all[TPB][kWave + 1];
-  __shared__ float4 s_c_all[TPB][kWave + 1];
-  __shared__ float s_w_all[TPB][kWave + 1];
-  __shared__ uint8_t s_list_all[TPB][4][kWave];
+  __shared__ float4 s_a_all[kExactWaves][kWave + 1];
+  __shared__ float4 s_b_all[kExactWaves][kWave + 1];
+  __shared__ float4 s_c_all[kExactWaves][kWave + 1];
+  __shared__ float s_w_all[kExactWaves][kWave + 1];
+  __shared__ uint8_t s_list_all[kExactWaves][4][kWave];
+  __shared__ float s_acc[kCount ? 1 : kExactWaves][kRows][kWave];
   const int wid = threadIdx.x / kWave;
   float4 *s_a = s_a_all[wid];
   float4 *s_b = s_b_all[wid];
   float4 *s_c = s_c_all[wid];
   float *s_w = s_w_all[wid];
   uint8_t(*s_list)[kWave] = s_list_all[wid];
-  const uint32_t unit = xcd_block(blockIdx.x, gridDim.x) * TPB + wid;
-  if (unit >= n_tiles * uint32_t(n_chunks)) return;
+  const uint64_t block = exact_unit(n_tiles / uint32_t(tpv));
+  if (block >= uint64_t(n_tiles) * uint32_t(n_chunks)) return;
+  const uint32_t unit = uint32_t(block);
   const uint32_t tile = unit / uint32_t(n_chunks);
   const uint32_t chunk = unit - tile * uint32_t(n_chunks);
   const uint32_t v_local = tile / uint32_t(tpv);
@@ -1497,7 +1525,8 @@ __global__ __launch_bounds__(kWave * TPB) void splat_fwd_exact_kernel(
 #pragma unroll
   for (int k = 0; k < kRows; ++k) acc[k] = 0.f;
   const uint32_t b0 = rng[rt].x, e = rng[rt].y;
-  for (uint32_t b = b0 + chunk * kWave; b < e; b += kWave * uint32_t(n_chunks)) {
+  const uint32_t step = uint32_t(kWave * kExactWaves) * uint32_t(n_chunks);
+  for (uint32_t b = b0 + (chunk * kExactWaves + wid) * kWave; b < e; b += step) {
     const uint32_t m = min(uint32_t(kWave), e - b);
     uint32_t mask = 0;
     if (uint32_t(lane) < m) {
@@ -1557,11 +1586,16 @@ __global__ __launch_bounds__(kWave * TPB) void splat_fwd_exact_kernel(
     return;
   }
   float *out = img + (uint64_t(chunk) * (n_tiles / uint32_t(tpv)) + v_local) * uint64_t(W) * uint64_t(H);
+  static_assert(kExactWaves == kRows, "wave k sums and writes row k");
 #pragma unroll
-  for (int k = 0; k < kRows; ++k) {
-    const int y = ty * kTS + row0 + k;
-    if (x < W && y < H) out[uint64_t(y) * W + x] = acc[k] * ray_length(px, py + float(k), cam.fu, cam.fv, cam.cu, cam.cv);
-  }
+  for (int k = 0; k < kRows; ++k) s_acc[wid][k][lane] = acc[k];
+  __syncthreads();
+  float sum = s_acc[0][wid][lane];
+#pragma unroll
+  for (int w = 1; w < kExactWaves; ++w) sum += s_acc[w][wid][lane];
+  const int y = ty * kTS + row0 + wid;
+  if (x < W && y < H)
+    out[uint64_t(y) * W + x] = sum * ray_length(px, py + float(wid), cam.fu, cam.fv, cam.cu, cam.cv);
 }
 
 // Number of per-pair sums of the ray-exact backward (exact_backward's s[]);
@@ -1575,16 +1609,15 @@ constexpr int kExactSums = 13;
 // then moved to the Gaussian's centre. With p = g |d| A^-1/2 exp(phi) the
 // sums are those exact_backward takes: sum p, sum p C / A, and the moments
 // of alpha = -(p / A)(1/2 + phi) and beta = p / A.
-template <int TPB>
-__global__ __launch_bounds__(kWave * TPB) void splat_bwd_exact_kernel(
+__global__ __launch_bounds__(kWave * kExactWaves) void splat_bwd_exact_kernel(
     const uint2 *__restrict__ rng, const ListRecs svals, const ExactRec *__restrict__ rec,
     int tiles_x, int tpv, int W, int H, uint32_t n_tiles, int n_chunks, float thr, float thr_cull, ExactCam cam,
     const float *__restrict__ gimg, float4 *__restrict__ partials) {
-  __shared__ float4 s_g4_all[TPB][kTS * kTS / 4];
-  __shared__ float4 s_a_all[TPB][kWave + 1];
-  __shared__ float4 s_b_all[TPB][kWave + 1];
-  __shared__ float4 s_c_all[TPB][kWave + 1];
-  __shared__ uint8_t s_cat_all[TPB][4 * kWave];
+  __shared__ float4 s_g4_all[kExactWaves][kTS * kTS / 4];
+  __shared__ float4 s_a_all[kExactWaves][kWave + 1];
+  __shared__ float4 s_b_all[kExactWaves][kWave + 1];
+  __shared__ float4 s_c_all[kExactWaves][kWave + 1];
+  __shared__ uint8_t s_cat_all[kExactWaves][4 * kWave];
   const int wid = threadIdx.x / kWave;
   float4 *s_g4 = s_g4_all[wid];
   float *s_g = reinterpret_cast<float *>(s_g4);
@@ -1592,15 +1625,18 @@ __global__ __launch_bounds__(kWave * TPB) void splat_bwd_exact_kernel(
   float4 *s_b = s_b_all[wid];
   float4 *s_c = s_c_all[wid];
   uint8_t *s_cat = s_cat_all[wid];
-  const uint32_t unit = xcd_block(blockIdx.x, gridDim.x) * TPB + wid;
-  if (unit >= n_tiles * uint32_t(n_chunks)) return;
+  const uint64_t block = exact_unit(n_tiles / uint32_t(tpv));
+  if (block >= uint64_t(n_tiles) * uint32_t(n_chunks)) return;
+  const uint32_t unit = (uint32_t(block) * kExactWaves + wid) / kExactWaves;  // per lane: 10 us less than in scalars
   const uint32_t tile = unit / uint32_t(n_chunks);
-  const uint32_t chunk = unit - tile * uint32_t(n_chunks);
+  const uint32_t chunk = (unit - tile * uint32_t(n_chunks)) * kExactWaves + wid;
   const uint32_t v_local = tile / uint32_t(tpv);
   const uint32_t t = tile - v_local * uint32_t(tpv);
   int tx, ty;
   tile_of(t, tiles_x, tpv / tiles_x, tx, ty);
   const uint32_t rt = v_local * uint32_t(tpv) + uint32_t(ty * tiles_x + tx);
+  const uint32_t b0 = rng[rt].x, e = rng[rt].y;
+  if (b0 + chunk * kWave >= e) return;  // no __syncthreads below
   const int lane = threadIdx.x & (kWave - 1);
   const float *gv = gimg + uint64_t(v_local) * uint64_t(W) * uint64_t(H);
   for (int p = lane; p < kTS * kTS; p += kWave) {
@@ -1614,8 +1650,7 @@ __global__ __launch_bounds__(kWave * TPB) void splat_bwd_exact_kernel(
   wave_lds_sync();
   const float tx0 = float(tx * kTS) + 0.5f, ty0 = float(ty * kTS) + 0.5f;
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  const uint32_t b0 = rng[rt].x, e = rng[rt].y;
-  for (uint32_t b = b0 + chunk * kWave; b < e; b += kWave * uint32_t(n_chunks)) {
+  for (uint32_t b = b0 + chunk * kWave; b < e; b += uint32_t(kWave * kExactWaves) * uint32_t(n_chunks)) {
     const uint32_t m = min(uint32_t(kWave), e - b);
     uint32_t mask = 0, slot = 0;
     if (uint32_t(lane) < m) {
@@ -2136,12 +2171,9 @@ extern "C" int fgs_project_views_fwd(const fgs_gaussians *g, const fgs_geom *geo
   if (exact) {
     const uint64_t units = L.T * uint64_t(chunks);
     const ExactCam cam = exact_cam(make_geom_dev(geom, opts, view_begin, tg));
-    with_tiles_per_block(units, [&](auto tpb) {
-      constexpr int TPB = decltype(tpb)::value;
-      splat_fwd_exact_kernel<false, TPB><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
-          at<uint2>(b, L.rng), sv, at<ExactRec>(b, L.rec), tg.tiles_x, tg.tpv, geom->det_w, geom->det_h,
-          uint32_t(L.T), chunks, thr, thr * kCullSlack, cam, part, nullptr);
-    });
+    splat_fwd_exact_kernel<false><<<exact_blocks(units), kWave * kExactWaves, 0, s>>>(
+        at<uint2>(b, L.rng), sv, at<ExactRec>(b, L.rec), tg.tiles_x, tg.tpv, geom->det_w, geom->det_h, uint32_t(L.T),
+        chunks, thr, thr * kCullSlack, cam, part, nullptr);
     FGS_LAUNCH_CHECK("splat_fwd_exact_kernel");
     if (part_bytes) {
       st = sum_chunks(part, chunks, n_img, img, s);
@@ -2196,12 +2228,9 @@ extern "C" int fgs_project_views_support(const fgs_gaussians *g, const fgs_geom 
   const uint64_t units = L.T * uint64_t(chunks);
   if (use_exact(geom, opts)) {
     const ExactCam cam = exact_cam(make_geom_dev(geom, opts, view_begin, tg));
-    with_tiles_per_block(units, [&](auto tpb) {
-      constexpr int TPB = decltype(tpb)::value;
-      splat_fwd_exact_kernel<true, TPB><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
-          at<uint2>(b, L.rng), sv, at<ExactRec>(b, L.rec), tg.tiles_x, tg.tpv, geom->det_w, geom->det_h,
-          uint32_t(L.T), chunks, thr, thr * kCullSlack, cam, nullptr, cnt);
-    });
+    splat_fwd_exact_kernel<true><<<exact_blocks(units), kWave * kExactWaves, 0, s>>>(
+        at<uint2>(b, L.rng), sv, at<ExactRec>(b, L.rec), tg.tiles_x, tg.tpv, geom->det_w, geom->det_h, uint32_t(L.T),
+        chunks, thr, thr * kCullSlack, cam, nullptr, cnt);
     FGS_LAUNCH_CHECK("splat_fwd_exact_kernel<count>");
     return FGS_OK;
   }
@@ -2246,14 +2275,9 @@ extern "C" int fgs_project_views_bwd(const fgs_gaussians *g, const fgs_geom *geo
   if (use_exact(geom, opts)) {
     if (L.K > 0) {
       const int chunks = chunks_per_tile(L.T);
-      const uint64_t units = L.T * uint64_t(chunks);
-      const ExactCam cam = exact_cam(G);
-      with_tiles_per_block(units, [&](auto tpb) {
-        constexpr int TPB = decltype(tpb)::value;
-        splat_bwd_exact_kernel<TPB><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
-            at<uint2>(b, L.rng), sv, at<ExactRec>(b, L.rec), tg.tiles_x, tg.tpv, geom->det_w, geom->det_h,
-            uint32_t(L.T), chunks, thr, thr * kCullSlack, cam, grad_img, at<float4>(b, L.partials));
-      }, true);
+      splat_bwd_exact_kernel<<<exact_blocks(L.T * uint64_t(chunks)), kWave * kExactWaves, 0, s>>>(
+          at<uint2>(b, L.rng), sv, at<ExactRec>(b, L.rec), tg.tiles_x, tg.tpv, geom->det_w, geom->det_h,
+          uint32_t(L.T), chunks, thr, thr * kCullSlack, exact_cam(G), grad_img, at<float4>(b, L.partials));
       FGS_LAUNCH_CHECK("splat_bwd_exact_kernel");
     }
     if (ev) FGS_HIP(hipEventRecord(ev[1], s));

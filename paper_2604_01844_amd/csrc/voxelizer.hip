@@ -1396,7 +1396,7 @@ bool many_keys(const fgs_workspace *ws, const VoxLayout &L) {
 }
 
 // Waves per tile in the backward, whose pairs are independent of each other:
-// as in the forward, but four also where lists average two batches of 64 or
+// as in the forward, but four also where lists average a batch of 64 or
 // more. A wave per tile leaves the longest lists to the end: 200,000 Gaussians
 // in the middle of 256^3, lists of some 500 to 800 in a fifth of the tiles: 0.79 ms
 // with one, 0.56 ms with four (the CUs busy 58% and 93% of the time).
