@@ -455,6 +455,44 @@ __device__ __forceinline__ bool unit_of_wave(const Units &U, uint32_t n_tiles, i
   return unit < nu;
 }
 
+// Without units (8,192 tiles or more): a wave per tile, or four, which take
+// the batches of its list in turn. With one, the longest lists end last, the
+// more so the fewer tiles there are for each wave that the chip holds; with four, a short
+// list leaves waves without a batch, and each prepares the tile for itself.
+// So four from a mean length of T / 256 keys on, 256 (a batch for
+// each wave) where there are 65,536 tiles or more. Forward and backward with their
+// binning, detectors of 512 x 512, one wave and four: 50,000 Gaussians of sigma 0.03, 75
+// views 7.00 and 6.07 ms, 8 views 1.61 and 0.81; 12,000, 8 views 0.47 and
+// 0.29, 32 views 0.91 and 0.78; below the line 5,000 in 75 views 0.92 and
+// 1.00, 2,000 of sigma 0.1 in 75 views 2.00 and 2.08. 500,000 in 4 views of
+// 2048 x 2048: 38.5 and 35.3 ms.
+constexpr uint64_t kShareAlways = 0, kShareNever = ~0ull;
+struct Share {
+  uint64_t from;  // keys from which four waves share a tile; kShareAlways and kShareNever: known on the host
+  unsigned blocks;
+};
+// At a fixed key capacity the count is known on the device only: the launch
+// is sized for sharing, and the blocks past the others' end return.
+inline Share share_rule(uint64_t T, uint64_t K, bool capacity) {
+  const unsigned one = unsigned((T + 3) / 4);
+  if (T >= (1ull << 32) / (4 * kWave)) return {kShareNever, one};  // work-items of a launch
+  const uint64_t from = T * (T < 65536 ? T : 65536) / 256;
+  if (capacity) return {from, unsigned(T)};
+  return K >= from ? Share{kShareAlways, unsigned(T)} : Share{kShareNever, one};
+}
+// The tile of this wave and its first batch; false past the last tile.
+template <int TPB>
+__device__ __forceinline__ bool tile_of_wave(uint64_t share_from, const uint32_t *kdev, uint32_t n_tiles, int wid,
+                                             bool &share, uint32_t &tile, uint32_t &batch) {
+  share = TPB == 4 && share_from != kShareNever && (share_from == kShareAlways || kdev[0] >= share_from);
+  const uint32_t per = share ? 1u : uint32_t(TPB), nb = (n_tiles + per - 1) / per;
+  if (blockIdx.x >= nb) return false;
+  const uint32_t b = xcd_block(blockIdx.x, nb);
+  batch = share ? uint32_t(wid) : 0u;
+  tile = uint32_t(__builtin_amdgcn_readfirstlane(int(share ? b : b * uint32_t(TPB) + uint32_t(wid))));
+  return tile < n_tiles;
+}
+
 // One workgroup of 1024 threads, T <= 8192 tiles (8 per thread).
 __global__ __launch_bounds__(1024) void unit_offsets_kernel(const uint2 *__restrict__ rng, uint32_t T, uint32_t cap,
                                                            uint32_t *__restrict__ first, uint32_t *__restrict__ tile) {
@@ -758,7 +796,7 @@ __global__ __launch_bounds__(kWave * TPB) __attribute__((amdgpu_waves_per_eu(7, 
                                                            const SplatRec *__restrict__ rec,
                                                            const uint32_t *__restrict__ kdev, uint64_t split_from,
                                                            int tiles_x, int tpv, int W, int H,
-                                                           uint32_t n_tiles, int n_chunks, Units U, float thr,
+                                                           uint32_t n_tiles, Units U, uint64_t share_from, float thr,
                                                            float log2_tau, int no_cull,
                                                            float *__restrict__ img,
                                                            unsigned long long *__restrict__ counter) {
@@ -773,31 +811,29 @@ __global__ __launch_bounds__(kWave * TPB) __attribute__((amdgpu_waves_per_eu(7, 
   uint8_t(*s_list)[kWave] = s_list_all[wid][0], (*s_inner)[kWave] = s_list_all[wid][kLists - 1];
   const bool split = kSplit == kSplitAlways || (kSplit == kSplitByCount && uint64_t(kdev[0]) >= split_from);
   const float margin = thr * (kCullSlack - 1.f);
-  // work unit: a piece of a tile's list (U.first), or (tile, chunk) where
-  // chunk c takes batches c, c + n_chunks, ...; each writes its own partial
-  // image when there are several per tile
-  // everything about the unit is the same across the wave (scalar registers)
-  uint32_t unit, tile, chunk, b_first, b_end, stride;
+  // work unit: a piece of a tile's list (U.first) with a partial image of its
+  // own, or a tile, whole or shared with the block's other waves; everything
+  // about it is the same across the wave (scalar registers)
+  bool share = false;
+  uint32_t unit, tile, b_first, b_end, stride;
   if (U.first) {
     if (!unit_of_wave<TPB>(U, n_tiles, wid, unit)) return;
     tile = uint32_t(__builtin_amdgcn_readfirstlane(int(U.tile[unit])));
-    chunk = unit - U.first[tile];
+    const uint32_t chunk = unit - U.first[tile];
     const uint32_t lo = rng[tile].x, hi = rng[tile].y, per = unit_keys(hi - lo);
     b_first = lo + chunk * per;
     b_end = min(hi, b_first + per);
     stride = kWave;
   } else {
-    unit = uint32_t(__builtin_amdgcn_readfirstlane(int(xcd_block(blockIdx.x, gridDim.x) * TPB + wid)));
-    if (unit >= n_tiles * uint32_t(n_chunks)) return;
-    tile = unit / uint32_t(n_chunks);
-    chunk = unit - tile * uint32_t(n_chunks);
-    b_first = rng[tile].x + chunk * kWave;
+    uint32_t batch;
+    if (!tile_of_wave<TPB>(share_from, kdev, n_tiles, wid, share, tile, batch)) return;
+    unit = tile;
+    b_first = rng[tile].x + batch * kWave;
     b_end = rng[tile].y;
-    stride = kWave * uint32_t(n_chunks);
+    stride = share ? kWave * TPB : kWave;
   }
   b_first = uint32_t(__builtin_amdgcn_readfirstlane(int(b_first)));
   b_end = uint32_t(__builtin_amdgcn_readfirstlane(int(b_end)));
-  chunk = uint32_t(__builtin_amdgcn_readfirstlane(int(chunk)));
   const uint32_t v_local = tile / uint32_t(tpv);
   const uint32_t t = tile - v_local * uint32_t(tpv);
   const int ty = int(t) / tiles_x;
@@ -913,6 +949,22 @@ __global__ __launch_bounds__(kWave * TPB) __attribute__((amdgpu_waves_per_eu(7, 
   // half 0 adds half 1's sums of the same pixels (lane + 8) and writes
 #pragma unroll
   for (int k = 0; k < kFwdRows; ++k) acc[k] += __shfl_down(acc[k], 8, kWave);
+  if (share) {
+    // the waves' sums of each pixel meet in LDS in wave order
+    float *mine = reinterpret_cast<float *>(s_cw);
+#pragma unroll
+    for (int k = 0; k < kFwdRows; ++k)
+      if (!half) mine[(row0 + k) * kTS + col] = acc[k];
+    __syncthreads();
+    for (int p = int(threadIdx.x); p < kTS * kTS; p += kWave * TPB) {
+      float sum = 0.f;
+#pragma unroll
+      for (int w = 0; w < TPB; ++w) sum += reinterpret_cast<const float *>(s_rec_all[w][0])[p];
+      const int X0 = tx * kTS + (p & (kTS - 1)), Y0 = ty * kTS + p / kTS;
+      if (X0 < W && Y0 < H) img[uint64_t(v_local) * uint64_t(W) * uint64_t(H) + uint64_t(Y0) * W + X0] = sum;
+    }
+    return;
+  }
   if (half) return;
   if (U.first) {
     // the unit's own 16 x 16 slot; every pixel is written
@@ -921,7 +973,7 @@ __global__ __launch_bounds__(kWave * TPB) __attribute__((amdgpu_waves_per_eu(7, 
     for (int k = 0; k < kFwdRows; ++k) slot[(row0 + k) * kTS + col] = acc[k];
     return;
   }
-  float *out = img + (uint64_t(chunk) * (n_tiles / uint32_t(tpv)) + v_local) * uint64_t(W) * uint64_t(H);
+  float *out = img + uint64_t(v_local) * uint64_t(W) * uint64_t(H);
 #pragma unroll
   for (int k = 0; k < kFwdRows; ++k) {
     const int y = ty * kTS + row0 + k;
@@ -958,8 +1010,8 @@ __global__ __launch_bounds__(kWave * TPB)
     __attribute__((amdgpu_waves_per_eu(kSplit == kSplitNever ? 7 : 6, kSplit == kSplitNever ? 7 : 6)))
 void splat_bwd_kernel(
     const uint2 *__restrict__ rng, const ListRecs svals,
-    const SplatRec *__restrict__ rec, const uint32_t *__restrict__ kdev, uint64_t split_from, int tiles_x, int tpv, int W, int H, uint32_t n_tiles, int n_chunks,
-    Units U, float thr, float log2_tau, int no_cull, const float *__restrict__ gimg,
+    const SplatRec *__restrict__ rec, const uint32_t *__restrict__ kdev, uint64_t split_from, int tiles_x, int tpv, int W, int H, uint32_t n_tiles,
+    Units U, uint64_t share_from, float thr, float log2_tau, int no_cull, const float *__restrict__ gimg,
     float4 *__restrict__ partials) {
   // per pixel: g = dL/dI and g cc (cc: column relative to the quadrant
   // centre), so the row loop accumulates with three FMAs per pixel
@@ -978,10 +1030,10 @@ void splat_bwd_kernel(
   float4 *s_cw = s_cw_all[wid];
   float2 *s_xy = s_xy_all[wid];
   uint8_t *s_cat = s_cat_all[wid];
-  // work unit: a piece of a tile's list (U.first, tiles in row order), or
-  // (tile, chunk) where chunk c takes batches c, c + n_chunks, ... (each
-  // pair's sums go to its own slot, so units are independent). Everything
-  // about the unit is the same across the wave (kept in scalar registers).
+  // work unit: a piece of a tile's list (U.first, tiles in row order), or a
+  // tile, whole or shared with the block's other waves (each pair's sums go
+  // to its own slot, so they are independent). Everything about the unit is
+  // the same across the wave (kept in scalar registers).
   uint32_t unit, rt, v_local, b_first, b_end, stride;
   int tx, ty;
   if (U.first) {
@@ -998,17 +1050,17 @@ void splat_bwd_kernel(
     stride = kWave;
     if (b_first >= b_end) return;  // an empty tile: nothing to write
   } else {
-    unit = uint32_t(__builtin_amdgcn_readfirstlane(int(xcd_block(blockIdx.x, gridDim.x) * TPB + wid)));
-    if (unit >= n_tiles * uint32_t(n_chunks)) return;
-    const uint32_t tile = unit / uint32_t(n_chunks);
-    const uint32_t chunk = unit - tile * uint32_t(n_chunks);
+    bool share;
+    uint32_t tile, batch;
+    if (!tile_of_wave<TPB>(share_from, kdev, n_tiles, wid, share, tile, batch)) return;
     v_local = tile / uint32_t(tpv);
     const uint32_t t = tile - v_local * uint32_t(tpv);
     tile_of(t, tiles_x, tpv / tiles_x, tx, ty);
     rt = v_local * uint32_t(tpv) + uint32_t(ty * tiles_x + tx);
-    b_first = rng[rt].x + chunk * kWave;
+    b_first = rng[rt].x + batch * kWave;
     b_end = rng[rt].y;
-    stride = kWave * uint32_t(n_chunks);
+    stride = share ? kWave * TPB : kWave;
+    if (b_first >= b_end) return;
   }
   b_first = uint32_t(__builtin_amdgcn_readfirstlane(int(b_first)));
   b_end = uint32_t(__builtin_amdgcn_readfirstlane(int(b_end)));
@@ -2183,11 +2235,13 @@ extern "C" int fgs_project_views_fwd(const fgs_gaussians *g, const fgs_geom *geo
     const Units U = make_units(L, b, use_units(T, false));
     const uint64_t units = U.first ? L.n_units : L.T;
     const int no_cull = (opts->ablate & FGS_ABLATE_QUADRANT_CULL) ? 1 : 0;
+    const Share share = share_rule(L.T, L.K, ws->key_capacity > 0);
     auto launch = [&](auto mode, auto tpb) {
       constexpr int TPB = decltype(tpb)::value;
-      splat_fwd_kernel<false, decltype(mode)::value, TPB><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
+      const unsigned blocks = U.first ? grid_for(units, TPB) : share.blocks;
+      splat_fwd_kernel<false, decltype(mode)::value, TPB><<<blocks, kWave * TPB, 0, s>>>(
           at<uint2>(b, L.rng), sv, at<SplatRec>(b, L.rec), at<uint32_t>(b, L.kdev), kSplitForward * L.R, tg.tiles_x, tg.tpv,
-          geom->det_w, geom->det_h, uint32_t(L.T), 1, U, thr, log2_tau, no_cull, part, nullptr);
+          geom->det_w, geom->det_h, uint32_t(L.T), U, share.from, thr, log2_tau, no_cull, part, nullptr);
     };
     with_split(split_mode(L.K, kSplitForward * L.R, ws->key_capacity > 0, no_cull != 0), [&](auto mode) {
       if (tiles_per_block(units) > 1)
@@ -2238,7 +2292,7 @@ extern "C" int fgs_project_views_support(const fgs_gaussians *g, const fgs_geom 
   const uint64_t sunits = U.first ? L.n_units : L.T;
   splat_fwd_kernel<true, kSplitNever, 4><<<grid_for(sunits, 4), kWave * 4, 0, s>>>(
       at<uint2>(b, L.rng), sv, at<SplatRec>(b, L.rec), at<uint32_t>(b, L.kdev), 0, tg.tiles_x, tg.tpv, geom->det_w,
-      geom->det_h, uint32_t(L.T), 1, U, thr, log2_tau, 0, nullptr, cnt);
+      geom->det_h, uint32_t(L.T), U, kShareNever, thr, log2_tau, 0, nullptr, cnt);
   FGS_LAUNCH_CHECK("splat_fwd_kernel<count>");
   return FGS_OK;
 }
@@ -2305,14 +2359,15 @@ extern "C" int fgs_project_views_bwd(const fgs_gaussians *g, const fgs_geom *geo
     }
   } else if (L.K > 0) {
     const Units U = make_units(L, b, use_units(L.T, false));
-    const int chunks = U.first ? 1 : chunks_per_tile(L.T);
-    const uint64_t units = U.first ? L.n_units : L.T * uint64_t(chunks);
+    const uint64_t units = U.first ? L.n_units : L.T;
     const int no_cull = (opts->ablate & FGS_ABLATE_QUADRANT_CULL) ? 1 : 0;
+    const Share share = share_rule(L.T, L.K, ws->key_capacity > 0);
     auto launch = [&](auto mode, auto tpb) {
       constexpr int TPB = decltype(tpb)::value;
-      splat_bwd_kernel<decltype(mode)::value, TPB><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
+      const unsigned blocks = U.first ? grid_for(units, TPB) : share.blocks;
+      splat_bwd_kernel<decltype(mode)::value, TPB><<<blocks, kWave * TPB, 0, s>>>(
           at<uint2>(b, L.rng), sv, at<SplatRec>(b, L.rec), at<uint32_t>(b, L.kdev), kSplitBackward * L.R, tg.tiles_x, tg.tpv,
-          geom->det_w, geom->det_h, uint32_t(L.T), chunks, U, thr, log2_tau, no_cull, grad_img,
+          geom->det_w, geom->det_h, uint32_t(L.T), U, share.from, thr, log2_tau, no_cull, grad_img,
           at<float4>(b, L.partials));
     };
     with_split(split_mode(L.K, kSplitBackward * L.R, ws->key_capacity > 0, no_cull != 0), [&](auto mode) {
