@@ -674,12 +674,69 @@ __device__ __forceinline__ int quarter_lists(uint32_t mask, int lane, uint8_t *s
   return most;
 }
 
+// Tiles in descending order of the lengths of their lists, by classes of a
+// quarter of the mean length (all from eight times the mean on are one), in
+// grid order within a class. counts: [blocks][kLengthClasses].
+constexpr int kLengthClasses = 32;
+__device__ __forceinline__ uint32_t length_class(const uint32_t *start, uint32_t n_tiles, uint32_t t) {
+  const uint32_t mean = start[n_tiles] / n_tiles + 1u;
+  return uint32_t(kLengthClasses - 1) - min(4u * (start[t + 1] - start[t]) / mean, uint32_t(kLengthClasses - 1));
+}
+
+__global__ __launch_bounds__(1024) void tile_classes_kernel(const uint32_t *__restrict__ start, uint32_t n_tiles,
+                                                            uint32_t *__restrict__ counts) {
+  __shared__ uint32_t s_n[kLengthClasses];
+  if (threadIdx.x < kLengthClasses) s_n[threadIdx.x] = 0u;
+  __syncthreads();
+  const uint32_t t = blockIdx.x * 1024u + threadIdx.x;
+  if (t < n_tiles) atomicAdd(&s_n[length_class(start, n_tiles, t)], 1u);
+  __syncthreads();
+  if (threadIdx.x < kLengthClasses) counts[blockIdx.x * kLengthClasses + threadIdx.x] = s_n[threadIdx.x];
+}
+
+__global__ __launch_bounds__(1024) void tile_order_kernel(const uint32_t *__restrict__ start, uint32_t n_tiles,
+                                                          const uint32_t *__restrict__ counts,
+                                                          uint32_t *__restrict__ order) {
+  constexpr int kWaves = 1024 / kWave;
+  __shared__ uint32_t s_total[kLengthClasses], s_before[kLengthClasses], s_wave[kWaves][kLengthClasses];
+  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+  // each class: its tiles in the grid, and in the blocks before this one
+  if (threadIdx.x < kLengthClasses) s_total[threadIdx.x] = s_before[threadIdx.x] = 0u;
+  __syncthreads();
+  const uint32_t c0 = threadIdx.x % kLengthClasses;
+  uint32_t total = 0, before = 0;
+  for (uint32_t b = threadIdx.x / kLengthClasses; b < gridDim.x; b += 1024 / kLengthClasses) {
+    const uint32_t n = counts[b * kLengthClasses + c0];
+    total += n;
+    before += b < blockIdx.x ? n : 0u;
+  }
+  atomicAdd(&s_total[c0], total);
+  atomicAdd(&s_before[c0], before);
+  const uint32_t t = blockIdx.x * 1024u + threadIdx.x;
+  const bool ok = t < n_tiles;
+  const uint32_t c = ok ? length_class(start, n_tiles, t) : 0u;
+  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  uint32_t rank = 0;
+#pragma unroll
+  for (int k = 0; k < kLengthClasses; ++k) {
+    const uint64_t bal = __ballot(ok && c == uint32_t(k));
+    if (lane == 0) s_wave[wid][k] = uint32_t(__popcll(bal));
+    if (c == uint32_t(k)) rank = uint32_t(__popcll(bal & lt));
+  }
+  __syncthreads();
+  if (!ok) return;
+  uint32_t at = s_before[c] + rank;
+  for (uint32_t k = 0; k < c; ++k) at += s_total[k];
+  for (int w = 0; w < wid; ++w) at += s_wave[w][c];
+  order[at] = t;
+}
+
 // One wave per 8^3 tile; 16-lane group Q owns quarter Q, each lane one x-row
 // of 8 voxels, and walks its list of reached pairs in list order: the sums
 // are vox_fwd_kernel's, bit for bit. Bound by VALU issue. Measured with
 // 200,000 Gaussians at 256^3 in a body (sigma 3 voxels): 1.35 ms with whole
 // tiles, compare and select, and a contiguous eighth of the grid per XCD; 0.65
-// ms now (the runs of blocks per XCD matter as much as the quarters there).
+// ms in runs of blocks per XCD, 0.46 by the order of tile_order_kernel.
 template <int TPB>
 __global__ __launch_bounds__(kWave * TPB) void vox_fwd_ordered_kernel(const uint32_t *__restrict__ start,
                                                                       const uint32_t *__restrict__ svals,
@@ -687,15 +744,16 @@ __global__ __launch_bounds__(kWave * TPB) void vox_fwd_ordered_kernel(const uint
                                                                       const float4 *__restrict__ a0,
                                                                       const float4 *__restrict__ a1,
                                                                       const uint32_t *__restrict__ gid, GridDev G,
-                                                                      uint32_t n_tiles, float thr_widen,
+                                                                      uint32_t n_tiles, const uint32_t *__restrict__ order, float thr_widen,
                                                                       float *__restrict__ vol) {
   // slot kWave: a pair that adds nothing
   __shared__ float4 s_all[TPB][3][kWave + 1];
   __shared__ uint8_t s_list_all[TPB][4 * kWave];
   const int wid = threadIdx.x / kWave;
   float4 *s_p = s_all[wid][0], *s_a0 = s_all[wid][1], *s_a1 = s_all[wid][2];
-  const uint32_t tile = xcd_run_block(blockIdx.x, gridDim.x) * TPB + wid;
-  if (tile >= n_tiles) return;
+  const uint32_t place = (order ? blockIdx.x : xcd_run_block(blockIdx.x, gridDim.x)) * TPB + wid;
+  if (place >= n_tiles) return;
+  const uint32_t tile = order ? uint32_t(__builtin_amdgcn_readfirstlane(int(order[place]))) : place;
   const int tx = int(tile % uint32_t(G.nt[0]));
   const int tyz = int(tile / uint32_t(G.nt[0]));
   const int ty = tyz % G.nt[1];
@@ -1395,6 +1453,18 @@ bool many_keys(const fgs_workspace *ws, const VoxLayout &L) {
   return ws->key_capacity == 0 && L.K >= kProductKeysPerRecord * L.N;
 }
 
+// Whether the list-order forward takes its tiles longest list first: where
+// lists average a batch of 64 or more and the chip holds a good share of the tiles
+// at once (up to 65,536: 320^3). In grid order the longest lists end last: 200,000
+// Gaussians in the middle of 256^3 0.67 ms, 0.46 longest first and 0.01 for
+// the order; with more tiles the end weighs little and neighbours no longer
+// share an L2 (500,000 of sigma 3 voxels at 512^3, forward and backward 3.57 and
+// 3.75 ms); with short lists the order costs what it gives (3,000 at 256^3
+// 0.41 and 0.42 ms).
+bool longest_first(const fgs_workspace *ws, const VoxLayout &L) {
+  return ws->key_capacity == 0 && L.T <= 65536 && L.K >= kWave * L.T;
+}
+
 // Waves per tile in the backward, whose pairs are independent of each other:
 // as in the forward, but four also where lists average a batch of 64 or
 // more. A wave per tile leaves the longest lists to the end: 200,000 Gaussians
@@ -1584,9 +1654,21 @@ int vox_forward(const fgs_gaussians *g, const fgs_grid *grid, const fgs_opts *op
   const uint64_t units = L.T * uint64_t(chunks);
   const float thr_widen = cull_widening(opts);
   if (chunks == 1 && !many_keys(ws, L)) {
+    uint32_t *order = nullptr;
+    if (longest_first(ws, L)) {
+      // in the room of the backward's partial sums, 10 words per pair
+      static_assert(10 * kWave >= 1 + kLengthClasses, "order and counts fit");
+      const unsigned blocks = grid_for(L.T, 1024);
+      order = at<uint32_t>(b, L.partials);
+      uint32_t *counts = order + L.T;
+      tile_classes_kernel<<<blocks, 1024, 0, s>>>(at<uint32_t>(b, L.start), uint32_t(L.T), counts);
+      FGS_LAUNCH_CHECK("tile_classes_kernel");
+      tile_order_kernel<<<blocks, 1024, 0, s>>>(at<uint32_t>(b, L.start), uint32_t(L.T), counts, order);
+      FGS_LAUNCH_CHECK("tile_order_kernel");
+    }
     vox_fwd_ordered_kernel<4><<<grid_for(L.T, 4), kWave * 4, 0, s>>>(
         at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
-        at<uint32_t>(b, L.gid), G, uint32_t(L.T), thr_widen, vol);
+        at<uint32_t>(b, L.gid), G, uint32_t(L.T), order, thr_widen, vol);
   } else if (chunks == 1) {
     vox_fwd_product_kernel<4><<<grid_for(L.T, 4), kWave * 4, 0, s>>>(
         at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
