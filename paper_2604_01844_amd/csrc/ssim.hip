@@ -264,14 +264,31 @@ extern "C" int fgs_ssim_loss_grad(const float *img, const float *gt, int32_t W, 
 //          and the gradient.
 // Every filter is x, then y, then z, taps in window order, so the result is
 // deterministic.
+//
+// Bound by VALU issue (stats: 82% of the busy clocks) and LDS together. A 2 x 1
+// output x filter by 208 threads, channel by channel, read 12 scalars per pair
+// from rows of stride 27, half of the LDS clocks in conflicts; tasks of four outputs
+// over all channels read 16 bytes at a time. 256^3: stats 0.325 -> 0.234 ms, grad 0.247
+// -> 0.220, 0.210 with neighbouring columns on one XCD, 0.200 with loads whose
+// address and range are worked out once per walk. Two columns per thread (half the y
+// filter's reads) measured 0.252 and 0.288 ms: 230 and 152 registers.
 
 namespace fgs {
 namespace {
 
 constexpr int kST = 16;              // tile side (x, y)
 constexpr int kSH = kST + 2 * kR;    // staged side (26)
+constexpr int kSP = 28;              // their row stride: rows start 16-byte aligned
 constexpr int kZC = 64;              // output slices per workgroup
 constexpr int kST2 = kST * kST;      // 256 threads, one column each
+constexpr int kQuads = kST / 4;      // groups of four outputs in a filtered row
+
+// LDS of a workgroup: the staged slice and its rows after the x filter.
+template <int CH>
+struct SliceLds {
+  float sp[CH][kSH][kSP];
+  float sh[CH][kSH][kST];
+};
 
 // The staged neighbourhood of one input slice, held in registers between its
 // global loads and its LDS stores: each thread loads kLoads of the slice's
@@ -284,75 +301,95 @@ struct SliceRegs {
   float v[kLoads][IN];
 };
 
-// Global loads of input slice zi (zero outside the grid). IN = 2: arrays a
-// and b; else the IN channels a[0..IN) with stride n.
-template <int IN>
-__device__ __forceinline__ void slice_load(const float *__restrict__ a, const float *__restrict__ b, uint64_t n,
-                                           int nx, int ny, int nz, int x0, int y0, int zi, SliceRegs<IN> &r) {
-  const bool zin = zi >= 0 && zi < nz;
-  const uint64_t zoff = uint64_t(zin ? zi : 0) * uint64_t(nx) * uint64_t(ny);
+// The thread's positions: offsets in a slice, and which of them are inside
+// the grid (bit l); the others read offset 0 and count as zero.
+struct SlicePositions {
+  uint64_t off[kLoads];
+  uint32_t inside;
+};
+
+__device__ __forceinline__ SlicePositions slice_positions(int nx, int ny, int x0, int y0) {
+  SlicePositions p;
+  p.inside = 0u;
 #pragma unroll
   for (int l = 0; l < kLoads; ++l) {
     const int i = int(threadIdx.x) + l * kST2;
     const int rr = i / kSH, c = i - rr * kSH;
     const int gx = x0 - kR + c, gy = y0 - kR + rr;
-    const bool in = zin && i < kSH * kSH && gx >= 0 && gx < nx && gy >= 0 && gy < ny;
-    const uint64_t q = zoff + uint64_t(in ? gy : 0) * uint64_t(nx) + uint64_t(in ? gx : 0);
+    const bool in = i < kSH * kSH && gx >= 0 && gx < nx && gy >= 0 && gy < ny;
+    p.off[l] = in ? uint64_t(gy) * uint64_t(nx) + uint64_t(gx) : 0u;
+    p.inside |= in ? 1u << l : 0u;
+  }
+  return p;
+}
+
+// Global loads of input slice zi, or of the nearest one in the grid. IN = 2:
+// arrays a and b; else the IN channels a[0..IN) with stride n.
+template <int IN>
+__device__ __forceinline__ void slice_load(const float *__restrict__ a, const float *__restrict__ b, uint64_t n,
+                                           uint64_t slice, int nz, int zi, const SlicePositions &p,
+                                           SliceRegs<IN> &r) {
+  const uint64_t zoff = uint64_t(min(max(zi, 0), nz - 1)) * slice;
+#pragma unroll
+  for (int l = 0; l < kLoads; ++l)
 #pragma unroll
     for (int ch = 0; ch < IN; ++ch) {
       const float *src = (IN == 2 && ch == 1) ? b : a + (IN == 2 ? 0 : uint64_t(ch) * n);
-      r.v[l][ch] = in ? src[q] : 0.f;
+      r.v[l][ch] = (src + zoff)[p.off[l]];
     }
-  }
 }
 
 // One staged slice through the x and y filters: the thread's column gets
 // f[c] for the CH channels. PRODUCTS: channels x, y, x^2, y^2, x y formed
 // from the two loaded arrays; else the CH loaded channels. Contains
 // barriers: every thread calls it.
-template <int CH, bool PRODUCTS, int IN>
-__device__ __forceinline__ void slice_filter_2d(const SliceRegs<IN> &r, const Window &win,
-                                                float (*sp)[kSH][kSH + 1], float (*sh)[kSH][kST + 1], float f[CH]) {
-  __syncthreads();  // the previous slice's reads of sp and sh are done
+// The registers are free for the next slice once load_next() is called.
+template <int CH, bool PRODUCTS, int IN, typename LoadNext>
+__device__ __forceinline__ void slice_filter_2d(const SliceRegs<IN> &r, uint32_t inside, const Window &win,
+                                                SliceLds<CH> &lds, float f[CH], LoadNext &&load_next) {
+  __syncthreads();  // the previous slice's reads are done
 #pragma unroll
   for (int l = 0; l < kLoads; ++l) {
     const int i = int(threadIdx.x) + l * kST2;
     if (i < kSH * kSH) {
       const int rr = i / kSH, c = i - rr * kSH;
-      if (PRODUCTS) {
-        const float xv = r.v[l][0], yv = r.v[l][IN - 1];
-        sp[0][rr][c] = xv;
-        sp[1][rr][c] = yv;
-        sp[2][rr][c] = xv * xv;
-        sp[3][rr][c] = yv * yv;
-        sp[4][rr][c] = xv * yv;
+      const bool in = (inside >> l) & 1u;
+      if constexpr (PRODUCTS) {
+        const float xv = in ? r.v[l][0] : 0.f, yv = in ? r.v[l][IN - 1] : 0.f;
+        lds.sp[0][rr][c] = xv;
+        lds.sp[1][rr][c] = yv;
+        lds.sp[2][rr][c] = xv * xv;
+        lds.sp[3][rr][c] = yv * yv;
+        lds.sp[4][rr][c] = xv * yv;
       } else {
 #pragma unroll
-        for (int ch = 0; ch < CH; ++ch) sp[ch][rr][c] = r.v[l][ch < IN ? ch : 0];
+        for (int ch = 0; ch < CH; ++ch) lds.sp[ch][rr][c] = in ? r.v[l][ch < IN ? ch : 0] : 0.f;
       }
     }
   }
+  load_next();
   __syncthreads();
-  // x filter: thread t < 208 takes row t / 8 and the two neighbouring
-  // outputs c0, c0 + 1 (c0 = 2 (t % 8)), which share 10 of their 11 inputs:
-  // 12 LDS reads per channel for two outputs
-  if (threadIdx.x < kSH * kST / 2) {
-    const int rr = int(threadIdx.x) / (kST / 2), c0 = 2 * (int(threadIdx.x) % (kST / 2));
-    // one channel at a time (the ring already holds 11 CH registers)
+  // x filter: a task is four neighbouring outputs of one row and channel,
+  // from 14 inputs in 16-byte reads
+  constexpr int kTasks = CH * kSH * kQuads;
 #pragma unroll 1
-    for (int ch = 0; ch < CH; ++ch) {
-      float v[kWin + 1];
+  for (int i = int(threadIdx.x); i < kTasks; i += kST2) {
+    const float *in = &lds.sp[0][0][0] + (i / kQuads) * kSP + 4 * (i % kQuads);
+    float v[16];
 #pragma unroll
-      for (int j = 0; j <= kWin; ++j) v[j] = sp[ch][rr][c0 + j];
-      float a0 = 0.f, a1 = 0.f;
-#pragma unroll
-      for (int k = 0; k < kWin; ++k) {
-        a0 = fmaf(win.w[k], v[k], a0);
-        a1 = fmaf(win.w[k], v[k + 1], a1);
-      }
-      sh[ch][rr][c0] = a0;
-      sh[ch][rr][c0 + 1] = a1;
+    for (int j = 0; j < 4; ++j) {
+      const float4 q = reinterpret_cast<const float4 *>(in)[j];
+      v[4 * j] = q.x, v[4 * j + 1] = q.y, v[4 * j + 2] = q.z, v[4 * j + 3] = q.w;
     }
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int k = 0; k < kWin; ++k) {
+      o.x = fmaf(win.w[k], v[k], o.x);
+      o.y = fmaf(win.w[k], v[k + 1], o.y);
+      o.z = fmaf(win.w[k], v[k + 2], o.z);
+      o.w = fmaf(win.w[k], v[k + 3], o.w);
+    }
+    reinterpret_cast<float4 *>(&lds.sh[0][0][0])[i] = o;
   }
   __syncthreads();
   const int tx = threadIdx.x & (kST - 1), ty = threadIdx.x / kST;
@@ -361,31 +398,47 @@ __device__ __forceinline__ void slice_filter_2d(const SliceRegs<IN> &r, const Wi
 #pragma unroll
   for (int k = 0; k < kWin; ++k)
 #pragma unroll
-    for (int ch = 0; ch < CH; ++ch) f[ch] = fmaf(win.w[k], sh[ch][ty + k][tx], f[ch]);
+    for (int ch = 0; ch < CH; ++ch) f[ch] = fmaf(win.w[k], lds.sh[ch][ty + k][tx], f[ch]);
+}
+
+// The workgroup's column: neighbours, which read each other's halos at the
+// same time, share an XCD's L2.
+struct Column {
+  int x, y, z;
+  uint32_t index;
+};
+__device__ __forceinline__ Column column_of_block() {
+  const uint32_t n = gridDim.x * gridDim.y * gridDim.z;
+  const uint32_t b = xcd_block((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, n);
+  const uint32_t yz = b / gridDim.x;
+  return {int(b - yz * gridDim.x), int(yz % gridDim.y), int(yz / gridDim.y), b};
 }
 
 // Walks input slices z0 - 5 .. z1 + 4 of the workgroup's chunk [z0, z1): ring
 // slot j of the unrolled loop holds input slice base + j. The loads of slice
-// k + 1 are issued before slice k is filtered. After the slice k (counted
-// from the chunk's first input slice) is filtered, output slice z0 + k - 10
-// is complete: emit(zo, m) receives its z-filtered channels.
-template <int CH, bool PRODUCTS, int IN, typename Emit>
+// k + 1 are issued before slice k is filtered, and before them those of
+// fetch(zo) for the output slice zo = z0 + k - 10, which is complete after
+// slice k (counted from the chunk's first input slice): emit(zo, m, fetched)
+// receives its z-filtered channels.
+template <int CH, bool PRODUCTS, int IN, typename Fetch, typename Emit>
 __device__ __forceinline__ void zring_walk(const float *__restrict__ a, const float *__restrict__ b, uint64_t n,
                                            int nx, int ny, int nz, int x0, int y0, int z0, int z1,
-                                           const Window &win, float (*sp)[kSH][kSH + 1],
-                                           float (*sh)[kSH][kST + 1], Emit &&emit) {
+                                           const Window &win, SliceLds<CH> &lds, Fetch &&fetch, Emit &&emit) {
   float ring[kWin][CH];
   const int n_in = (z1 - z0) + 2 * kR;
-  SliceRegs<IN> cur, nxt;
-  slice_load<IN>(a, b, n, nx, ny, nz, x0, y0, z0 - kR, cur);
+  const uint64_t slice = uint64_t(nx) * uint64_t(ny);
+  const SlicePositions pos = slice_positions(nx, ny, x0, y0);
+  SliceRegs<IN> cur;
+  slice_load<IN>(a, b, n, slice, nz, z0 - kR, pos, cur);
   for (int base = 0; base < n_in; base += kWin) {
 #pragma unroll
     for (int j = 0; j < kWin; ++j) {
       const int k = base + j;
       if (k >= n_in) break;  // uniform over the workgroup
-      if (k + 1 < n_in) slice_load<IN>(a, b, n, nx, ny, nz, x0, y0, z0 - kR + k + 1, nxt);
-      slice_filter_2d<CH, PRODUCTS, IN>(cur, win, sp, sh, ring[j]);
-      cur = nxt;
+      const int zi = z0 - kR + k;
+      const auto fetched = fetch(max(zi - kR, z0));
+      slice_filter_2d<CH, PRODUCTS, IN>(cur, zi >= 0 && zi < nz ? pos.inside : 0u, win, lds, ring[j],
+                                        [&] { slice_load<IN>(a, b, n, slice, nz, zi + 1, pos, cur); });
       if (k >= 2 * kR) {
         float m[CH];
 #pragma unroll
@@ -396,7 +449,7 @@ __device__ __forceinline__ void zring_walk(const float *__restrict__ a, const fl
 #pragma unroll
           for (int ch = 0; ch < CH; ++ch) m[ch] = fmaf(win.w[t], ring[slot][ch], m[ch]);
         }
-        emit(z0 + k - 2 * kR, m);
+        emit(zi - kR, m, fetched);
       }
     }
   }
@@ -406,16 +459,16 @@ __global__ __launch_bounds__(kST2) void ssim3d_stats_kernel(const float *__restr
                                                             const float *__restrict__ gt, int nx, int ny, int nz,
                                                             Window win, float c1, float c2,
                                                             float *__restrict__ g, float *__restrict__ partial) {
-  __shared__ float sp[5][kSH][kSH + 1];
-  __shared__ float sh[5][kSH][kST + 1];
+  __shared__ alignas(16) SliceLds<5> lds;
   __shared__ float sw[kST2 / 64];
   const uint64_t n = uint64_t(nx) * uint64_t(ny) * uint64_t(nz);
-  const int x0 = blockIdx.x * kST, y0 = blockIdx.y * kST;
-  const int z0 = blockIdx.z * kZC, z1 = min(z0 + kZC, nz);
+  const Column col = column_of_block();
+  const int x0 = col.x * kST, y0 = col.y * kST;
+  const int z0 = col.z * kZC, z1 = min(z0 + kZC, nz);
   const int X = x0 + int(threadIdx.x & (kST - 1)), Y = y0 + int(threadIdx.x / kST);
   const bool mine = X < nx && Y < ny;
   CompSum acc;
-  zring_walk<5, true, 2>(vol, gt, n, nx, ny, nz, x0, y0, z0, z1, win, sp, sh, [&](int zo, const float *m) {
+  zring_walk<5, true, 2>(vol, gt, n, nx, ny, nz, x0, y0, z0, z1, win, lds, [](int) { return 0; }, [&](int zo, const float *m, int) {
     if (!mine) return;
     const float mx = m[0], my = m[1];
     const float A = fmaf(2.f * mx, my, c1);
@@ -433,26 +486,39 @@ __global__ __launch_bounds__(kST2) void ssim3d_stats_kernel(const float *__restr
     }
   });
   const float t = block_sum_f32<kST2>(acc.value(), sw);
-  if (threadIdx.x == 0) partial[(uint64_t(blockIdx.z) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = t;
+  if (threadIdx.x == 0) partial[col.index] = t;
 }
 
 __global__ __launch_bounds__(kST2) void ssim3d_grad_kernel(const float *__restrict__ vol,
                                                            const float *__restrict__ gt, int nx, int ny, int nz,
                                                            Window win, const float *__restrict__ g, float coef,
                                                            int accumulate, float *__restrict__ grad) {
-  __shared__ float sp[3][kSH][kSH + 1];
-  __shared__ float sh[3][kSH][kST + 1];
+  __shared__ alignas(16) SliceLds<3> lds;
   const uint64_t n = uint64_t(nx) * uint64_t(ny) * uint64_t(nz);
-  const int x0 = blockIdx.x * kST, y0 = blockIdx.y * kST;
-  const int z0 = blockIdx.z * kZC, z1 = min(z0 + kZC, nz);
+  const Column col = column_of_block();
+  const int x0 = col.x * kST, y0 = col.y * kST;
+  const int z0 = col.z * kZC, z1 = min(z0 + kZC, nz);
   const int X = x0 + int(threadIdx.x & (kST - 1)), Y = y0 + int(threadIdx.x / kST);
   const bool mine = X < nx && Y < ny;
-  zring_walk<3, false, 3>(g, nullptr, n, nx, ny, nz, x0, y0, z0, z1, win, sp, sh, [&](int zo, const float *m) {
-    if (!mine) return;
-    const uint64_t q = (uint64_t(zo) * uint64_t(ny) + uint64_t(Y)) * uint64_t(nx) + uint64_t(X);
-    const float gq = coef * (m[0] + 2.f * vol[q] * m[1] + gt[q] * m[2]);
-    grad[q] = accumulate ? grad[q] + gq : gq;
-  });
+  // the thread's voxel of the slice that its walk completes
+  const uint64_t slice = uint64_t(nx) * uint64_t(ny), at = mine ? uint64_t(Y) * uint64_t(nx) + uint64_t(X) : 0u;
+  struct Fetched {
+    float x, y, g;
+  };
+  zring_walk<3, false, 3>(
+      g, nullptr, n, nx, ny, nz, x0, y0, z0, z1, win, lds,
+      [&](int zo) {
+        const uint64_t q = uint64_t(zo) * slice + at;
+        return Fetched{vol[q], gt[q], accumulate ? grad[q] : 0.f};
+      },
+      [&](int zo, const float *m, const Fetched &f) {
+        if (!mine) return;
+        const float gq = coef * (m[0] + 2.f * f.x * m[1] + f.y * m[2]);
+        {
+#pragma clang fp contract(off)  // one value whether it is added to grad or stored
+          grad[uint64_t(zo) * slice + at] = accumulate ? f.g + gq : gq;
+        }
+      });
 }
 
 }  // namespace
