@@ -194,6 +194,16 @@ __device__ __forceinline__ uint64_t pair_count(uint64_t n, const uint32_t *n_dev
   return n_dev ? min(n, uint64_t(*n_dev)) : n;
 }
 
+// The tile of this block. Consecutive tiles write neighbouring words of the
+// table and neighbouring runs of the output, often less than a line each: on one
+// XCD its L2 joins them, on eight each line went out in parts. Per pass over the
+// (tile, Gaussian) pairs of 500,000 Gaussians at 512^3: scatter 5.16 -> 3.01 ms,
+// histogram 1.15 -> 0.63 ms.
+__device__ __forceinline__ uint32_t tile_of_block(uint64_t n) {
+  const uint32_t tiles = uint32_t((n + kTile - 1) / kTile);
+  return blockIdx.x < tiles ? xcd_block(blockIdx.x, tiles) : blockIdx.x;
+}
+
 template <int NB>
 __global__ __launch_bounds__(kThreads) void rs_hist_kernel(const uint32_t *__restrict__ keys,
                                                            uint64_t n_cap, const uint32_t *__restrict__ n_dev,
@@ -205,7 +215,8 @@ __global__ __launch_bounds__(kThreads) void rs_hist_kernel(const uint32_t *__res
   const uint64_t n = pair_count(n_cap, n_dev);
   for (int i = threadIdx.x; i < kBins; i += kThreads) h[i] = 0;
   __syncthreads();
-  const uint64_t base = uint64_t(blockIdx.x) * kTile;
+  const uint32_t tile = tile_of_block(n);
+  const uint64_t base = uint64_t(tile) * kTile;
   // all of the thread's loads first, so their latencies overlap
   uint32_t kk[kItems];
 #pragma unroll
@@ -219,7 +230,7 @@ __global__ __launch_bounds__(kThreads) void rs_hist_kernel(const uint32_t *__res
     if (idx < n) atomicAdd(&h[(kk[j] >> shift) & mask], 1u);
   }
   __syncthreads();
-  for (uint32_t d = threadIdx.x; d <= mask; d += kThreads) hist[uint64_t(d) * n_tiles + blockIdx.x] = h[d];
+  for (uint32_t d = threadIdx.x; d <= mask; d += kThreads) hist[uint64_t(d) * n_tiles + tile] = h[d];
 }
 
 // Stable scatter of one pass. Tile t covers input [t*4096, t*4096 + 4096);
@@ -237,6 +248,7 @@ __global__ __launch_bounds__(kThreads) void rs_scatter_kernel(
   const uint64_t n = pair_count(n_cap, n_dev);
   // a tile past the device count (a grid sized for the capacity) moves nothing
   if (uint64_t(blockIdx.x) * kTile >= n) return;
+  const uint32_t tile = tile_of_block(n);
   constexpr int kBins = 1 << NB;
   __shared__ uint32_t cnt[kWaves][kBins];
   __shared__ uint32_t s_local[kBins];     // tile-local start of each digit's run
@@ -249,7 +261,7 @@ __global__ __launch_bounds__(kThreads) void rs_scatter_kernel(
   for (int i = threadIdx.x; i < kWaves * kBins; i += kThreads) (&cnt[0][0])[i] = 0;
   __syncthreads();
 
-  const uint64_t wbase = uint64_t(blockIdx.x) * kTile + uint64_t(wid) * (kItems * 64);
+  const uint64_t wbase = uint64_t(tile) * kTile + uint64_t(wid) * (kItems * 64);
   const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   uint32_t k[kItems], v[kItems], rank[kItems];
   // all of the wave's loads first, so their latencies overlap
@@ -288,7 +300,7 @@ __global__ __launch_bounds__(kThreads) void rs_scatter_kernel(
 #pragma unroll
   for (int q = 0; q < kPer; ++q) {  // the table loads first, so they overlap
     const int d = threadIdx.x * per_thread + q;
-    if (q < per_thread && d < bins) gstart[q] = hist_scanned[uint64_t(d) * n_tiles + blockIdx.x];
+    if (q < per_thread && d < bins) gstart[q] = hist_scanned[uint64_t(d) * n_tiles + tile];
   }
 #pragma unroll
   for (int q = 0; q < kPer; ++q) {
@@ -334,7 +346,7 @@ __global__ __launch_bounds__(kThreads) void rs_scatter_kernel(
     }
   }
   __syncthreads();
-  const uint64_t tbase = uint64_t(blockIdx.x) * kTile;
+  const uint64_t tbase = uint64_t(tile) * kTile;
   const int nt = tbase < n ? int(min(uint64_t(kTile), n - tbase)) : 0;
   for (int i = threadIdx.x; i < nt; i += kThreads) {
     const uint32_t key = s_keys[i];
