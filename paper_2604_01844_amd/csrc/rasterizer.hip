@@ -936,7 +936,13 @@ __global__ __launch_bounds__(kWave * TPB) __attribute__((amdgpu_waves_per_eu(7, 
         if (kCount) acc[k] += (arg[k] >= q.w) ? 1.f : 0.f;
         else ex[k] = __builtin_amdgcn_exp2f(arg[k]);
       }
-      if (!kCount) masked_fma8(acc, c.w, arg, ex, q.w);
+      // a wave alone on its SIMD (TPB = 1) waits for the mask at every term:
+      // compare and select there (2,000 Gaussians at 64 x 64: 11.7 us, 14.2 masked)
+      if (!kCount && TPB > 1) masked_fma8(acc, c.w, arg, ex, q.w);
+      if (!kCount && TPB == 1) {
+#pragma unroll
+        for (int k = 0; k < kFwdRows; ++k) acc[k] = fmaf(c.w, (arg[k] >= q.w) ? ex[k] : 0.f, acc[k]);
+      }
     }
     wave_lds_sync();
   }
