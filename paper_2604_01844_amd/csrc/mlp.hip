@@ -72,13 +72,15 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(const uint16_t *__restrict
   if (m0 >= M) return;
   const int kofs = 8 * (lane >> 5);
   const uint16_t *arow = A + int64_t(m0 + (lane & 31)) * K + kofs;
+  // N is a multiple of 32: a column tile is whole or absent, for the whole wave;
+  // an absent one repeats column 0 and is not stored, which keeps the loads
+  // below free of branches and of the waits between them
   const uint16_t *brow[kNT];
   bool in[kNT];
 #pragma unroll
   for (int t = 0; t < kNT; ++t) {
-    const int col = n0 + 32 * t + (lane & 31);
-    in[t] = col < N;
-    brow[t] = B + int64_t(in[t] ? col : 0) * K + kofs;
+    in[t] = n0 + 32 * t < N;
+    brow[t] = B + int64_t(in[t] ? n0 + 32 * t + (lane & 31) : 0) * K + kofs;
   }
   f32x16 acc[kNT];
 #pragma unroll
@@ -91,7 +93,6 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(const uint16_t *__restrict
   struct Group {
     bf16x8 a[kGroup], b[kGroup][kNT];
   };
-  const i16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
   auto load = [&](Group &g, int k) {
 #pragma unroll
     for (int u = 0; u < kGroup; ++u) {
@@ -99,7 +100,7 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(const uint16_t *__restrict
       g.a[u] = load8(arow + k + 16 * u);
 #pragma unroll
       for (int t = 0; t < kNT; ++t)
-        g.b[u][t] = in[t] ? load8(brow[t] + k + 16 * u) : __builtin_bit_cast(bf16x8, zero8);
+        g.b[u][t] = load8(brow[t] + k + 16 * u);
     }
   };
   auto multiply = [&](const Group &g, int k) {
@@ -119,19 +120,23 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(const uint16_t *__restrict
     load(even, k + 32 * kGroup);
     multiply(odd, k + 16 * kGroup);
   }
-  // what the results need is loaded before the first of them is stored: the
-  // compiler keeps loads behind stores that could alias them, 64 waits in a
-  // row (50,016 rows: three forward products 92 -> 79 us, two data products 82 -> 77)
+  // what the results need is loaded before the first of them is stored, and
+  // without branches on the lane: a load behind a store that could alias it, or
+  // behind such a branch, waited by itself, 64 in a row (50,016 rows: three forward
+  // products 92 -> 82 us, two data products 82 -> 39)
   float bias[kNT], z[EPI == kEpiData ? kNT : 1][16];
 #pragma unroll
   for (int t = 0; t < kNT; ++t) {
+    if (!in[t]) break;
     const int col = n0 + 32 * t + (lane & 31);
-    if (EPI == kEpiFwd) bias[t] = in[t] ? e.bias[col] : 0.f;
+    if (EPI == kEpiFwd) bias[t] = e.bias[col];
     if constexpr (EPI == kEpiData) {
+      const float *mz = e.mask_z ? e.mask_z + int64_t(m0 + 4 * (lane >> 5)) * N + col : nullptr;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = m0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        z[t][r] = e.mask_z && in[t] ? e.mask_z[int64_t(row) * N + col] : 1.f;
+      for (int r = 0; r < 16; ++r) z[t][r] = 1.f;
+      if (e.mask_z) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z[t][r] = mz[int64_t(8 * (r >> 2) + (r & 3)) * N];
       }
     }
   }
@@ -140,7 +145,7 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(const uint16_t *__restrict
 #pragma unroll
   for (int t = 0; t < kNT; ++t) {
     const int col = n0 + 32 * t + (lane & 31);
-    if (col >= N) continue;
+    if (!in[t]) break;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int row = m0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
