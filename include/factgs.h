@@ -230,7 +230,8 @@ typedef struct {
  * ascending Gaussian index after the stable sort) in an order fixed by the
  * list and the launch shape alone: each 8-lane half of a quadrant group
  * takes alternate entries, the interior variant takes a batch's interior
- * pairs first, a few-tile call sums its work units' partials in unit order.
+ * pairs first, waves that share a tile's list add their sums in wave order, a
+ * few-tile call sums its work units' partials in unit order.
  * No atomics: deterministic and bit-reproducible for a given call shape.
  * Synchronisation: waits on `stream` once to read the pair count, unless
  * ws->key_capacity > 0 (then not at all).

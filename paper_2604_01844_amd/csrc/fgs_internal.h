@@ -15,15 +15,12 @@
 namespace fgs {
 
 // Independent tiles (one per wave) per workgroup of the pixel and voxel
-// kernels: 16 when a call has enough tiles to give every CU several
-// workgroups (which is what lets a CU hold enough waves), fewer for small
-// calls (one view, a crop) so that their waves spread over all CUs.
-// A workgroup's LDS is released only when all its waves are done, so a wave
-// that finishes its tile early leaves its slot idle until the workgroup's
-// longest tile ends: the splat kernels take at most 4 (small_blocks).
-inline int tiles_per_block(uint64_t n_tiles, bool small_blocks = false) {
-  return n_tiles >= 16384 ? (small_blocks ? 4 : 16) : (n_tiles >= 4096 ? 4 : 1);
-}
+// kernels: 4 when a call has enough tiles to give every CU several
+// workgroups, 1 for small calls (one view, a crop) so that their waves spread
+// over all CUs. A workgroup's LDS is released only when all its waves are done,
+// so a wave that finishes its tile early leaves its slot idle until the
+// workgroup's longest tile ends: more than 4 was slower in every kernel.
+inline int tiles_per_block(uint64_t n_tiles) { return n_tiles >= 4096 ? 4 : 1; }
 
 // Waves per tile: a call with few tiles (one view, a crop) splits each
 // tile's list over several waves (strided batches), so that the longest
@@ -110,16 +107,14 @@ __device__ __forceinline__ uint32_t turned_block(uint32_t b, uint32_t n) {
   return (r + 1u) * kRound > n ? b : r * kRound + (b + 9u * r) % kRound;
 }
 
-// Calls f(std::integral_constant<int, TPB>) with TPB = tiles_per_block(n_tiles, small_blocks).
+// Calls f(std::integral_constant<int, TPB>) with TPB = tiles_per_block(n_tiles).
 template <typename F>
-void with_tiles_per_block(uint64_t n_tiles, F &&f, bool small_blocks = false) {
-  switch (tiles_per_block(n_tiles, small_blocks)) {
-    case 16: f(std::integral_constant<int, 16>()); break;
-    case 4: f(std::integral_constant<int, 4>()); break;
-    default: f(std::integral_constant<int, 1>()); break;
-  }
+void with_tiles_per_block(uint64_t n_tiles, F &&f) {
+  if (tiles_per_block(n_tiles) == 4)
+    f(std::integral_constant<int, 4>());
+  else
+    f(std::integral_constant<int, 1>());
 }
-
 
 // ------------------------------------------------------------------ errors
 

@@ -18,8 +18,9 @@
 //                         ascending Gaussian index; no depth key (the sum is
 //                         order-free).
 //   5. ranges kernel      per-(view, tile) [start, end) by boundary detection.
-//   6. splat kernel       one 64-lane wave per 16x16 tile, up to 4 tiles per
-//                         workgroup; batches of 64 records staged in LDS;
+//   6. splat kernel       one 64-lane wave per 16x16 tile, four where lists are
+//                         long (or, with few tiles, a wave per piece of a
+//                         list); batches of 64 records staged in LDS;
 //                         each record is tested against the tile's four 8x8
 //                         quadrants and a 16-lane group walks one quadrant's
 //                         list, each lane a column of 8 pixels; the Gaussian

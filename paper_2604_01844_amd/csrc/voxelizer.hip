@@ -8,17 +8,22 @@
 //                   voxel-unit inverse covariance pre-scaled by -log2(e)/2,
 //                   half-extents in voxels and the 3D rectangle of 8^3-voxel
 //                   tiles its box touches;
-//   count kernel    one wave per Gaussian: of the rectangle's tiles, those
-//                   its support ellipsoid actually reaches (exact box test;
-//                   about 57% of the box's tiles for the standard scan);
+//   count kernel    a wave per Gaussian with a large rectangle, for four of
+//                   them with small ones: of the rectangle's tiles, those the
+//                   support ellipsoid actually reaches (bounds at the tile's
+//                   centre decide most, the exact box test the rest; about 57%
+//                   of the box's tiles for the standard scan);
 //   scan / emit     keys of the reached tiles; the sort's value is the
 //                   emission slot, whose Gaussian is gid[slot];
 //   stable radix sort / ranges as in the rasterizer;
-//   forward         one wave per 8^3 tile; each lane owns one x-row of 8
-//                   voxels; records staged in LDS in batches of 64;
-//   backward        one wave per tile; each lane owns one (tile, Gaussian)
-//                   pair and sums the ten moments sum g e {1, d, d d^T} over
-//                   the tile's 512 voxels into the pair's emission slot; per
+//   forward         one wave per 8^3 tile (grids with few tiles: several, with
+//                   partial volumes); 16 lanes walk a quarter's list, each one
+//                   x-row of 8 voxels; records staged in LDS in batches of 64;
+//                   where Gaussians span many tiles, interior quarters by
+//                   products along the row;
+//   backward        one or four waves per tile; each lane owns one (tile,
+//                   Gaussian) pair and sums the ten moments sum g e {1, d, d d^T}
+//                   over the tile's 512 voxels into the pair's emission slot; per
 //                   Gaussian, its contiguous slots are reduced in a fixed
 //                   order and the chain rule applied.
 #include "fgs_internal.h"
@@ -1759,7 +1764,7 @@ int vox_backward(const fgs_gaussians *g, const fgs_grid *grid, const fgs_opts *o
           at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
           at<uint32_t>(b, L.gid), G, uint32_t(L.T), cull_widening(opts), grad_vol, at<float2>(b, L.partials));
     } else with_tiles_per_block(units, [&](auto tpb) {
-      constexpr int TPB = decltype(tpb)::value > 4 ? 4 : decltype(tpb)::value;
+      constexpr int TPB = decltype(tpb)::value;
       vox_bwd_kernel<TPB><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
           at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
           at<uint32_t>(b, L.gid), G, uint32_t(L.T), chunks, grad_vol, at<float2>(b, L.partials));
