@@ -603,7 +603,7 @@ __global__ __launch_bounds__(kWave * TPB) void vox_fwd_kernel(const uint32_t *__
 // Tiles per Gaussian from which the forward evaluates interior quarters by
 // products along the row (vox_fwd_product_kernel).
 // Products pay where most quarters are interior: with sigma 15 voxels (1,100
-// tiles per Gaussian) two thirds are and the forward takes 37.3 ms against
+// tiles per Gaussian) two thirds are and the forward takes 32.4 ms against
 // 47 in list order (500,000 Gaussians, 512^3); with sigma 3 (20 tiles) a tenth
 // are, and the two lists per quarter cost more than they save (1.23 against
 // 0.65 ms, 200,000 at 256^3). They change the order of the sums.
@@ -830,7 +830,7 @@ __global__ __launch_bounds__(kWave * TPB) void vox_fwd_ordered_kernel(const uint
 // against 8.4 for the boundary path (v_exp_f32 takes two issue slots), whose
 // arithmetic is vox_fwd_kernel's. Bound by VALU issue. Measured with
 // 500,000 Gaussians at 512^3 (sigma 15 voxels): 54.3 ms with a whole tile per
-// pair and compare and select, 37.3 ms now.
+// pair and compare and select, 32.4 ms now.
 template <int TPB>
 __global__ __launch_bounds__(kWave * TPB) void vox_fwd_product_kernel(const uint32_t *__restrict__ start,
                                                                       const uint32_t *__restrict__ svals,
@@ -936,17 +936,21 @@ __global__ __launch_bounds__(kWave * TPB) void vox_fwd_product_kernel(const uint
     wave_lds_sync();
   }
   // half 0 adds half 1's sums of the same rows (lane + 8); half 0 writes the first row, half 1 the second
+  // (chosen from the sums: chosen from acc itself, the compiler indexed it by the lane, and
+  // every entry of the lists went through memory)
+  float sum[kVT];
 #pragma unroll
-  for (int w = 0; w < 2; ++w)
-#pragma unroll
-    for (int k = 0; k < kVT; ++k) acc[w][k] += __shfl_xor(acc[w][k], 8, kWave);
+  for (int k = 0; k < kVT; ++k) {
+    const float s0 = acc[0][k] + __shfl_xor(acc[0][k], 8, kWave), s1 = acc[1][k] + __shfl_xor(acc[1][k], 8, kWave);
+    sum[k] = half ? s1 : s0;
+  }
   const int zw = z + half;
   if (y < G.dims[1] && zw < G.dims[2]) {
     float *row = vol + (uint64_t(zw) * G.dims[1] + y) * uint64_t(G.dims[0]);
 #pragma unroll
     for (int k = 0; k < kVT; ++k) {
       const int x = tx * kVT + k;
-      if (x < G.dims[0]) row[x] = half ? acc[1][k] : acc[0][k];
+      if (x < G.dims[0]) row[x] = sum[k];
     }
   }
 }
