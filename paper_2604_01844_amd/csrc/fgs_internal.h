@@ -331,6 +331,11 @@ __device__ __forceinline__ void masked_sums4(float (&A)[8], int at, float &R0, f
 #undef FGS_TERM
 }
 
+// Whether index i + d (d = 0 or 1) lies in [0, n), in unsigned arithmetic: a
+// coordinate far outside, or infinite, converts to the last int, and i + 1 there
+// must count as outside, not as the first one.
+__device__ __forceinline__ bool index_inside(int i, uint32_t d, int n) { return uint32_t(i) + d < uint32_t(n); }
+
 // log2(e): exp(x) = exp2(x * log2(e)). Kernels pre-scale quadratic forms by
 // -log2(e)/2 so that the Gaussian factor is a single v_exp_f32.
 constexpr float kLog2e = 1.4426950408889634f;

@@ -290,13 +290,15 @@ __device__ __forceinline__ float trilinear_at(const float *__restrict__ vol, con
   const int x0 = int(fx), y0 = int(fy), z0 = int(fz);
   const float a = cx - fx, b = cy - fy, g = cz - fz;
   float acc = 0.f;
-  if (x0 >= 0 && x0 + 1 < G.dims[0] && y0 >= 0 && y0 + 1 < G.dims[1] && z0 >= 0 && z0 + 1 < G.dims[2])
+  auto both = [](int i, int n) { return index_inside(i, 0, n) && index_inside(i, 1, n); };
+  if (both(x0, G.dims[0]) && both(y0, G.dims[1]) && both(z0, G.dims[2]))
     return blend(corners_at(vol, G, cx, cy, cz));
   for (int dz = 0; dz < 2; ++dz)
     for (int dy = 0; dy < 2; ++dy)
       for (int dx = 0; dx < 2; ++dx) {
+        if (!index_inside(x0, dx, G.dims[0]) || !index_inside(y0, dy, G.dims[1]) || !index_inside(z0, dz, G.dims[2]))
+          continue;
         const int x = x0 + dx, y = y0 + dy, z = z0 + dz;
-        if (x < 0 || x >= G.dims[0] || y < 0 || y >= G.dims[1] || z < 0 || z >= G.dims[2]) continue;
         const float w = (dx ? a : 1.f - a) * (dy ? b : 1.f - b) * (dz ? g : 1.f - g);
         acc = fmaf(w, vol[(int64_t(z) * G.dims[1] + y) * G.dims[0] + x], acc);
       }
