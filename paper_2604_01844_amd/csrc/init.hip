@@ -302,8 +302,10 @@ __global__ __launch_bounds__(256) void fdk_backproject_kernel(FdkGeom G, const f
           }
         } else {
           const float *qv = q + uint64_t(v) * HW;
-          auto at = [&](int uu, int ww) -> float {
-            return (uu >= 0 && uu < G.W && ww >= 0 && ww < G.H) ? qv[uint64_t(ww) * G.W + uu] : 0.f;
+          auto at = [&](uint32_t du, int w0, uint32_t dw) -> float {
+            return index_inside(u0, du, G.W) && index_inside(w0, dw, G.H)
+                       ? qv[uint64_t(uint32_t(w0) + dw) * G.W + (uint32_t(u0) + du)]
+                       : 0.f;
           };
 #pragma unroll 1
           for (int k = 0; k < RUN; ++k) {
@@ -311,8 +313,8 @@ __global__ __launch_bounds__(256) void fdk_backproject_kernel(FdkGeom G, const f
             const float w0f = floorf(w);
             const int w0 = int(w0f);
             const float fw = w - w0f;
-            const float top = fmaf(fu, at(u0 + 1, w0), gu * at(u0, w0));
-            const float bot = fmaf(fu, at(u0 + 1, w0 + 1), gu * at(u0, w0 + 1));
+            const float top = fmaf(fu, at(1, w0, 0), gu * at(0, w0, 0));
+            const float bot = fmaf(fu, at(1, w0, 1), gu * at(0, w0, 1));
             const float val = fmaf(fw, bot, (1.f - fw) * top);
 #pragma unroll
             for (int j = 0; j < RUN; ++j) acc[j] = j == k ? fmaf(wt2, val, acc[j]) : acc[j];
@@ -438,8 +440,8 @@ __device__ __forceinline__ float trilinear(const float *__restrict__ vol, const 
   for (int dz = 0; dz < 2; ++dz)
     for (int dy = 0; dy < 2; ++dy)
       for (int dx = 0; dx < 2; ++dx) {
+        if (!index_inside(i0, dx, dims[0]) || !index_inside(j0, dy, dims[1]) || !index_inside(k0, dz, dims[2])) continue;
         const int x = i0 + dx, y = j0 + dy, z = k0 + dz;
-        if (x < 0 || x >= dims[0] || y < 0 || y >= dims[1] || z < 0 || z >= dims[2]) continue;
         const float wgt = (dx ? a : 1.f - a) * (dy ? b : 1.f - b) * (dz ? g : 1.f - g);
         acc = fmaf(wgt, vol[(int64_t(z) * dims[1] + y) * dims[0] + x], acc);
       }

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import synth_inputs as si
 
 pytestmark = pytest.mark.gpu
@@ -35,3 +36,24 @@ def test_patch_of_a_far_mean_is_zero():
     assert torch.equal(x[rest], ref[rest])
     assert (x[far][:, :512] == 0).all() and x.shape[1] == K_IN
     assert torch.equal(x[:, 512:515], (2 * mean.T).to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("dims", [(17, 17, 17), (165, 161, 161)])  # runs of 4 and of 16 voxels
+def test_fdk_voxels_beside_the_source(dims):
+    """A plane of voxels 2^-25 in front of the source, whose rays meet the
+    detector's plane up to 2^31 pixels away, and voxels behind the source. A
+    pixel coordinate is 5,120 t0 at most in front of that plane, a few ulps of
+    which are 1e-3 pixel, and neighbouring samples differ by about their own size."""
+    import paper_2604_01844_amd as fgs
+    h = 1.0 / 16
+    at = 8  # this plane's x is 1/2 - 2^-25, exactly
+    gr = dict(origin=(0.5 - 2.0 ** -25 - (at + 0.5) * h, -0.5 * dims[1] * h, -0.5 * dims[2] * h), spacing=(h,) * 3, dims=dims)
+    gd = dict(mode="cone", sod=0.5, sdd=2.0, det_w=64, det_h=48, pitch_u=2.0 / 160, pitch_v=2.0 / 160, off_u=0.0, off_v=0.0)
+    ang = np.zeros(1, dtype=np.float32)
+    img = (1.0 + 0.1 * si.normals((1, 48, 64), 83)).astype(np.float32)
+    vol = fgs.fdk(torch.from_numpy(img).to(DEV), fgs.Geometry.from_dict(gd, ang), fgs.Grid.from_dict(gr)).cpu().numpy()
+    ref = oracle.fdk(img, gd, ang, gr)
+    assert np.abs(ref[..., :at]).max() > 0 and np.abs(ref[..., at]).max() > 1e12
+    assert (vol[..., at + 1:] == 0).all() and ((ref == 0) <= (vol == 0)).all()
+    assert oracle.rel_l2(vol[..., :at], ref[..., :at]) < 1e-3
+    np.testing.assert_allclose(vol[..., at], ref[..., at], rtol=1e-3)
