@@ -1478,10 +1478,12 @@ bool longest_first(const fgs_workspace *ws, const VoxLayout &L) {
 // as in the forward, but four also where lists average a batch of 64 or
 // more. A wave per tile leaves the longest lists to the end: 200,000 Gaussians
 // in the middle of 256^3, lists of some 500 to 800 in a fifth of the tiles: 0.79 ms
-// with one, 0.56 ms with four (the CUs busy 58% and 93% of the time).
+// with one, 0.56 ms with four (the CUs busy 58% and 93% of the time). From 2^24 tiles on
+// four waves each would be 2^32 work-items, more than a launch holds.
 int backward_chunks(const fgs_workspace *ws, const VoxLayout &L) {
   const int c = chunks_per_tile(L.T);
-  return c == 1 && ws->key_capacity == 0 && L.K >= kWave * L.T ? 4 : c;
+  const bool fits = L.T < (uint64_t(1) << 32) / (4 * kWave);
+  return c == 1 && fits && ws->key_capacity == 0 && L.K >= kWave * L.T ? 4 : c;
 }
 
 template <typename T>
