@@ -609,6 +609,20 @@ __global__ __launch_bounds__(kWave * TPB) void vox_fwd_kernel(const uint32_t *__
 // 0.65 ms, 200,000 at 256^3). They change the order of the sums.
 constexpr uint64_t kProductKeysPerRecord = 96;
 
+// Which of the two kinds of kernel a call without chunks takes: the host knows
+// where it read the pair count back; at a fixed key capacity it launches both
+// (unless the capacity itself is below the line), and the blocks of one return
+// at once. Every kernel of the product kind runs where the count reaches
+// `from`, the others elsewhere, so a call's bits do not depend on how its
+// lists were laid out.
+struct VoxPick {
+  const uint32_t *kdev;  // null: picked on the host
+  uint64_t from;
+};
+__device__ __forceinline__ bool picked(const VoxPick &pick, bool product) {
+  return !pick.kdev || (uint64_t(pick.kdev[0]) >= pick.from) == product;
+}
+
 // A pair's exponent over the tile, arg(k, Y, Z) = a00 + a10 Y + a01 Z + a20 Y^2
 // + a11 Y Z + a02 Z^2 + k (e0 + e1 Y + e2 Z) + c k^2 for voxel k of the x-row
 // (Y, Z), half-integers from the tile's centre.
@@ -750,7 +764,8 @@ __global__ __launch_bounds__(kWave * TPB) void vox_fwd_ordered_kernel(const uint
                                                                       const float4 *__restrict__ a1,
                                                                       const uint32_t *__restrict__ gid, GridDev G,
                                                                       uint32_t n_tiles, const uint32_t *__restrict__ order, float thr_widen,
-                                                                      float *__restrict__ vol) {
+                                                                      VoxPick pick, float *__restrict__ vol) {
+  if (!picked(pick, false)) return;
   // slot kWave: a pair that adds nothing
   __shared__ float4 s_all[TPB][3][kWave + 1];
   __shared__ uint8_t s_list_all[TPB][4 * kWave];
@@ -838,8 +853,9 @@ __global__ __launch_bounds__(kWave * TPB) void vox_fwd_product_kernel(const uint
                                                                       const float4 *__restrict__ a0,
                                                                       const float4 *__restrict__ a1,
                                                                       const uint32_t *__restrict__ gid, GridDev G,
-                                                                      uint32_t n_tiles, float thr_widen,
+                                                                      uint32_t n_tiles, float thr_widen, VoxPick pick,
                                                                       float *__restrict__ vol) {
+  if (!picked(pick, true)) return;
   // per batch slot (slot kWave: a pair that adds nothing): the form's
   // coefficients, the tile polynomial, rho exp2(c k^2), and (p, rho)
   __shared__ float4 s_all[TPB][6][kWave + 1];
@@ -991,9 +1007,10 @@ __global__ __launch_bounds__(kWave * TPB) void vox_bwd_kernel(const uint32_t *__
                                                          const float4 *__restrict__ a0,
                                                          const float4 *__restrict__ a1,
                                                          const uint32_t *__restrict__ gid,
-                                                         GridDev G, uint32_t n_tiles, int n_chunks,
+                                                         GridDev G, uint32_t n_tiles, int n_chunks, VoxPick pick,
                                                          const float *__restrict__ gvol,
                                                          float2 *__restrict__ partials) {
+  if (!picked(pick, false)) return;
   __shared__ float4 s_g4_all[TPB][2][kVT * kVT * kVT / 4];
   const int wid = threadIdx.x / kWave;
   float4 *s_g4 = s_g4_all[wid][0];
@@ -1223,9 +1240,10 @@ __global__ __launch_bounds__(kWave * TPB) __attribute__((amdgpu_waves_per_eu(5, 
                                                                       const float4 *__restrict__ a0,
                                                                       const float4 *__restrict__ a1,
                                                                       const uint32_t *__restrict__ gid, GridDev G,
-                                                                      uint32_t n_tiles, float thr_widen,
+                                                                      uint32_t n_tiles, float thr_widen, VoxPick pick,
                                                                       const float *__restrict__ gvol,
                                                                       float2 *__restrict__ partials) {
+  if (!picked(pick, true)) return;
   __shared__ float4 s_g4_all[TPB][2][kVT * kVT * kVT / 4];
   __shared__ uint32_t s_ring_all[TPB][2][2 * kWave];
   const int wid = threadIdx.x / kWave;
@@ -1456,10 +1474,9 @@ VoxLayout vox_layout(uint64_t N, uint64_t T, uint64_t K) {
 // The culling tests' slack on the pre-scaled exponent (negative).
 float cull_widening(const fgs_opts *o) { return -0.5f * kLog2e * o->kappa * o->kappa * (kCullSlack - 1.f); }
 
-// Whether the pairs read back from this call average kProductKeysPerRecord
-// tiles per Gaussian (at a fixed key capacity the count is not known here).
-bool many_keys(const fgs_workspace *ws, const VoxLayout &L) {
-  return ws->key_capacity == 0 && L.K >= kProductKeysPerRecord * L.N;
+// Pairs from which a call takes the product kernels (one wave per tile only).
+uint64_t product_from(const VoxLayout &L) {
+  return chunks_per_tile(L.T) == 1 ? kProductKeysPerRecord * L.N : ~uint64_t(0);
 }
 
 // Whether the list-order forward takes its tiles longest list first: where
@@ -1471,7 +1488,7 @@ bool many_keys(const fgs_workspace *ws, const VoxLayout &L) {
 // 3.75 ms); with short lists the order costs what it gives (3,000 at 256^3
 // 0.41 and 0.42 ms).
 bool longest_first(const fgs_workspace *ws, const VoxLayout &L) {
-  return ws->key_capacity == 0 && L.T <= 65536 && L.K >= kWave * L.T;
+  return ws->key_capacity == 0 && L.T <= 65536 && L.K >= kWave * L.T && L.K < product_from(L);
 }
 
 // Waves per tile in the backward, whose pairs are independent of each other:
@@ -1489,6 +1506,16 @@ int backward_chunks(const fgs_workspace *ws, const VoxLayout &L) {
 template <typename T>
 T *at(void *base, uint64_t off) {
   return reinterpret_cast<T *>(static_cast<char *>(base) + off);
+}
+
+// Calls list_order(pick) or product(pick) or, at a fixed key capacity that
+// reaches the line, both.
+template <typename F, typename P>
+void with_vox_pick(const fgs_workspace *ws, void *b, const VoxLayout &L, F &&list_order, P &&product) {
+  const bool reaches = L.K >= product_from(L), by_count = reaches && ws->key_capacity > 0;
+  const VoxPick pick{by_count ? at<uint32_t>(b, L.kdev) : nullptr, product_from(L)};
+  if (!reaches || by_count) list_order(pick);
+  if (reaches) product(pick);
 }
 
 int validate(const fgs_gaussians *g, const fgs_grid *grid, const fgs_opts *o, fgs_workspace *ws) {
@@ -1664,7 +1691,7 @@ int vox_forward(const fgs_gaussians *g, const fgs_grid *grid, const fgs_opts *op
   if (ev) FGS_HIP(hipEventRecord(ev[0], s));
   const uint64_t units = L.T * uint64_t(chunks);
   const float thr_widen = cull_widening(opts);
-  if (chunks == 1 && !many_keys(ws, L)) {
+  if (chunks == 1) {
     uint32_t *order = nullptr;
     if (longest_first(ws, L)) {
       // in the room of the backward's partial sums, 10 words per pair
@@ -1677,22 +1704,27 @@ int vox_forward(const fgs_gaussians *g, const fgs_grid *grid, const fgs_opts *op
       tile_order_kernel<<<blocks, 1024, 0, s>>>(at<uint32_t>(b, L.start), uint32_t(L.T), counts, order);
       FGS_LAUNCH_CHECK("tile_order_kernel");
     }
-    vox_fwd_ordered_kernel<4><<<grid_for(L.T, 4), kWave * 4, 0, s>>>(
-        at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
-        at<uint32_t>(b, L.gid), G, uint32_t(L.T), order, thr_widen, vol);
-  } else if (chunks == 1) {
-    vox_fwd_product_kernel<4><<<grid_for(L.T, 4), kWave * 4, 0, s>>>(
-        at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
-        at<uint32_t>(b, L.gid), G, uint32_t(L.T), thr_widen, vol);
-  } else
-  with_tiles_per_block(units, [&](auto tpb) {
-    constexpr int TPB = decltype(tpb)::value;
-    vox_fwd_kernel<false, TPB><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
-        at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
-        at<uint32_t>(b, L.gid), G, uint32_t(L.T), chunks, part, nullptr);
-  });
-  FGS_LAUNCH_CHECK("vox_fwd_kernel");
-  if (chunks > 1) {
+    with_vox_pick(
+        ws, b, L,
+        [&](const VoxPick &pick) {
+          vox_fwd_ordered_kernel<4><<<grid_for(L.T, 4), kWave * 4, 0, s>>>(
+              at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
+              at<uint32_t>(b, L.gid), G, uint32_t(L.T), order, thr_widen, pick, vol);
+        },
+        [&](const VoxPick &pick) {
+          vox_fwd_product_kernel<4><<<grid_for(L.T, 4), kWave * 4, 0, s>>>(
+              at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
+              at<uint32_t>(b, L.gid), G, uint32_t(L.T), thr_widen, pick, vol);
+        });
+    FGS_LAUNCH_CHECK("vox_fwd_ordered_kernel / vox_fwd_product_kernel");
+  } else {
+    with_tiles_per_block(units, [&](auto tpb) {
+      constexpr int TPB = decltype(tpb)::value;
+      vox_fwd_kernel<false, TPB><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
+          at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
+          at<uint32_t>(b, L.gid), G, uint32_t(L.T), chunks, part, nullptr);
+    });
+    FGS_LAUNCH_CHECK("vox_fwd_kernel");
     st = sum_chunks(part, chunks, n_vox, vol, s);
     if (st != FGS_OK) return st;
   }
@@ -1765,17 +1797,22 @@ int vox_backward(const fgs_gaussians *g, const fgs_grid *grid, const fgs_opts *o
   if (L.K > 0) {
     const int chunks = backward_chunks(ws, L);
     const uint64_t units = L.T * uint64_t(chunks);
-    if (chunks_per_tile(L.T) == 1 && many_keys(ws, L)) {
-      vox_bwd_product_kernel<4><<<grid_for(L.T, 4), kWave * 4, 0, s>>>(
-          at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
-          at<uint32_t>(b, L.gid), G, uint32_t(L.T), cull_widening(opts), grad_vol, at<float2>(b, L.partials));
-    } else with_tiles_per_block(units, [&](auto tpb) {
-      constexpr int TPB = decltype(tpb)::value;
-      vox_bwd_kernel<TPB><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
-          at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
-          at<uint32_t>(b, L.gid), G, uint32_t(L.T), chunks, grad_vol, at<float2>(b, L.partials));
-    });
-    FGS_LAUNCH_CHECK("vox_bwd_kernel");
+    with_vox_pick(
+        ws, b, L,
+        [&](const VoxPick &pick) {
+          with_tiles_per_block(units, [&](auto tpb) {
+            constexpr int TPB = decltype(tpb)::value;
+            vox_bwd_kernel<TPB><<<grid_for(units, TPB), kWave * TPB, 0, s>>>(
+                at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
+                at<uint32_t>(b, L.gid), G, uint32_t(L.T), chunks, pick, grad_vol, at<float2>(b, L.partials));
+          });
+        },
+        [&](const VoxPick &pick) {
+          vox_bwd_product_kernel<4><<<grid_for(L.T, 4), kWave * 4, 0, s>>>(
+              at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
+              at<uint32_t>(b, L.gid), G, uint32_t(L.T), cull_widening(opts), pick, grad_vol, at<float2>(b, L.partials));
+        });
+    FGS_LAUNCH_CHECK("vox_bwd_kernel / vox_bwd_product_kernel");
   }
   if (ev) FGS_HIP(hipEventRecord(ev[1], s));
   vox_grad_kernel<<<grid_for(uint64_t(g->n), kGradGauss), 256, 0, s>>>(*g, G, at<uint32_t>(b, L.offset),
