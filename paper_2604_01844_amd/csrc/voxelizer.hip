@@ -26,6 +26,8 @@
 //                   over the tile's 512 voxels into the pair's emission slot; per
 //                   Gaussian, its contiguous slots are reduced in a fixed
 //                   order and the chain rule applied.
+#include <algorithm>
+
 #include "fgs_internal.h"
 
 namespace fgs {
@@ -600,14 +602,17 @@ __global__ __launch_bounds__(kWave * TPB) void vox_fwd_kernel(const uint32_t *__
 // (interior). Both keep a margin of 0.1% of the kappa cutoff, far above
 // rounding, so every voxel keeps the decision that the per-voxel test makes.
 
-// Tiles per Gaussian from which the forward evaluates interior quarters by
-// products along the row (vox_fwd_product_kernel).
-// Products pay where most quarters are interior: with sigma 15 voxels (1,100
-// tiles per Gaussian) two thirds are and the forward takes 32.4 ms against
-// 47 in list order (500,000 Gaussians, 512^3); with sigma 3 (20 tiles) a tenth
-// are, and the two lists per quarter cost more than they save (1.23 against
-// 0.65 ms, 200,000 at 256^3). They change the order of the sums.
-constexpr uint64_t kProductKeysPerRecord = 96;
+// Tiles per Gaussian and pairs per tile from which interior quarters (forward)
+// and pairs (backward) are evaluated by products along the row. They change the
+// order of the sums. Products pay where many quarters are interior: Gaussians
+// all over 512^3, some 260 pairs per tile, forward and backward in list order and by
+// products: 24 tiles per Gaussian (sigma 3 voxels) 5.97 + 10.2 and 5.64 + 10.7 ms, 87
+// tiles 5.79 + 9.53 and 4.90 + 9.13, 130 tiles 5.67 + 9.44 and 4.63 + 8.63, 1,030 tiles
+// 5.01 + 8.45 and 3.49 + 7.41. And they pay where a list fills the backward's rounds of
+// 64, of which it makes two kinds: 130 tiles per Gaussian, 86 pairs per tile
+// 1.71 + 4.04 and 1.55 + 4.09 ms, 26 pairs 0.77 + 1.75 and 0.81 + 2.57, 9 pairs
+// 0.68 + 1.74 and 0.72 + 2.42.
+constexpr uint64_t kProductKeysPerRecord = 96, kProductKeysPerTile = kWave;
 
 // Which of the two kinds of kernel a call without chunks takes: the host knows
 // where it read the pair count back; at a fixed key capacity it launches both
@@ -1476,7 +1481,7 @@ float cull_widening(const fgs_opts *o) { return -0.5f * kLog2e * o->kappa * o->k
 
 // Pairs from which a call takes the product kernels (one wave per tile only).
 uint64_t product_from(const VoxLayout &L) {
-  return chunks_per_tile(L.T) == 1 ? kProductKeysPerRecord * L.N : ~uint64_t(0);
+  return chunks_per_tile(L.T) == 1 ? std::max(kProductKeysPerRecord * L.N, kProductKeysPerTile * L.T) : ~uint64_t(0);
 }
 
 // Whether the list-order forward takes its tiles longest list first: where

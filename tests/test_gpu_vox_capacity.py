@@ -18,8 +18,8 @@ NAMES = ("mean", "log_scale", "quat", "density")
 
 CASES = [
     # n, sigma, spread, half-width of the body, dims, tau, product
-    (1500, 0.06, 0.3, 0.15, (161, 163, 165), 0.0, True),   # lists of up to 1,000 and more
-    (1500, 0.06, 0.3, 0.15, (161, 163, 165), 2e-2, True),
+    (3500, 0.06, 0.3, 0.15, (161, 163, 165), 0.0, True),   # lists of up to 1,000 and more
+    (4500, 0.06, 0.3, 0.15, (161, 163, 165), 2e-2, True),
     (500, 0.08, 0.6, 0.2, (2049, 513, 8), 0.0, True),      # one layer of tiles
     (3000, 0.015, 0.3, 0.3, (161, 163, 165), 0.0, False),
 ]
@@ -35,14 +35,14 @@ def test_capacity_keeps_bits(n, sigma, sd, half, dims, tau, product):
     grid = fgs.Grid.from_dict(gr)
     ws = fgs.Workspace(DEV)
     vol = fgs.voxelize(*args, grid, tau=tau, ws=ws)
-    assert (ws.n_pairs >= 96 * n) == product
+    assert (ws.n_pairs >= max(96 * n, 64 * ws.s.n_tiles)) == product
     lists = fgs.binning_dump(ws)["tile_start"].diff()
     assert int(lists.max()) > (200 if product else 20)
     c = si.normals(grid.shape, 92)
     cd = torch.from_numpy(c).to(DEV)
     got = fgs.voxelize_backward(*args, grid, cd, tau=tau, recompute=False, ws=ws)
     # a capacity just enough, and one that reaches the line whatever the count
-    for cap in (ws.n_pairs, max(4 * ws.n_pairs, 128 * n)):
+    for cap in (ws.n_pairs, max(4 * ws.n_pairs, 128 * n, 128 * ws.s.n_tiles)):
         wc = fgs.Workspace(DEV)
         wc.set_capacity(cap)
         assert torch.equal(vol, fgs.voxelize(*args, grid, tau=tau, ws=wc))
@@ -57,14 +57,14 @@ def test_capacity_keeps_bits(n, sigma, sd, half, dims, tau, product):
 
 def test_capacity_too_small_bins_nothing():
     import paper_2604_01844_amd as fgs
-    n, dims = 300, (161, 163, 165)
+    n, dims = 4000, (161, 163, 165)
     gs = si.gaussians(n, 93, log_scale_mean=float(np.log(0.06)), lo=-0.15, hi=0.15)
     args = [torch.from_numpy(gs[k]).to(DEV) for k in NAMES]
     grid = fgs.Grid((-0.5,) * 3, (1.0 / 165,) * 3, dims)
     wc = fgs.Workspace(DEV)
-    wc.set_capacity(100 * n)  # past the line, below the call's pairs
+    wc.set_capacity(600000)  # past the line (592,704), below the call's pairs
     vol = fgs.voxelize(*args, grid, ws=wc)
     got = fgs.voxelize_backward(*args, grid, torch.ones(grid.shape, device=DEV), recompute=False, ws=wc)
     assert (vol == 0).all() and all((t == 0).all() for t in got)
     over, need = wc.overflowed()
-    assert over and need > 100 * n
+    assert over and need > 600000
