@@ -639,8 +639,10 @@ __device__ __forceinline__ void build_quad_lists(uint32_t mask, int lane, uint8_
 // pre-scaled form at the quadrant's centre: the form is concave, so its
 // tangent plane bounds it from above (not reached), and its value less every
 // term's largest drop bounds it from below (interior). Both keep a margin of
-// 0.1% of the kappa cutoff (margin < 0), far above the rounding of the
-// per-pixel exponent, so every pixel keeps the decision of the per-pixel test.
+// 0.1% of the kappa cutoff (margin < 0) and of 4e-6 of the terms' sizes, which
+// is above the rounding of these bounds and of the per-pixel exponent (in needles
+// the terms cancel, and the first margin alone is not), so every pixel keeps the
+// decision of the per-pixel test.
 //
 // Splitting pays when most quadrants are interior, i.e. when Gaussians span
 // many tiles: the forward does it in calls that average at least kSplitForward
@@ -671,9 +673,10 @@ void with_split(SplitMode mode, F &&f) {
     f(std::integral_constant<SplitMode, kSplitByCount>());
 }
 
-// The form over the tile whose centre is (cx, cy): value q and gradient g there.
+// The form over the tile whose centre is (cx, cy): value q and gradient g
+// there, and a bound on the rounding of its values over the tile.
 struct TileForm {
-  float q, gx, gy;
+  float q, gx, gy, err;
 };
 
 __device__ __forceinline__ TileForm tile_form(const float4 &c, float u, float v, float cx, float cy) {
@@ -682,6 +685,8 @@ __device__ __forceinline__ TileForm tile_form(const float4 &c, float u, float v,
   T.q = fmaf(dx, fmaf(c.x, dx, c.y * dy), c.z * dy * dy);
   T.gx = fmaf(2.f * c.x, dx, c.y * dy);
   T.gy = fmaf(2.f * c.z, dy, c.y * dx);
+  const float far = fmaxf(fabsf(dx), fabsf(dy)) + 7.5f;
+  T.err = 4e-6f * (fabsf(c.x) + fabsf(c.y) + fabsf(c.z)) * far * far;
   return T;
 }
 
@@ -695,8 +700,8 @@ __device__ __forceinline__ void quad_split(const TileForm &T, const float4 &c, f
     const float gx = fmaf(2.f * c.x, X, fmaf(c.y, Y, T.gx)), gy = fmaf(2.f * c.z, Y, fmaf(c.y, X, T.gy));
     const float q = fmaf(X, fmaf(c.x, X, fmaf(c.y, Y, T.gx)), fmaf(Y, fmaf(c.z, Y, T.gy), T.q));
     const float slope = 3.5f * (fabsf(gx) + fabsf(gy));
-    if (!(q + slope < thr + margin)) reach |= 1u << Q;
-    if (q - slope - drop >= thr - margin) inner |= 1u << Q;
+    if (!(q + slope < thr + margin - T.err)) reach |= 1u << Q;
+    if (q - slope - drop >= thr - margin + T.err) inner |= 1u << Q;
   }
   // the products down a column stay far from the ends of FP32's range: their
   // exponent is at most |threshold| + 49 |c|

@@ -599,8 +599,10 @@ __global__ __launch_bounds__(kWave * TPB) void vox_fwd_kernel(const uint32_t *__
 // come from the value and the gradient of the exponent at the quarter's
 // centre: the form is concave, so its tangent plane bounds it from above
 // (skip), and its value less every term's largest drop bounds it from below
-// (interior). Both keep a margin of 0.1% of the kappa cutoff, far above
-// rounding, so every voxel keeps the decision that the per-voxel test makes.
+// (interior). Both keep a margin of 0.1% of the kappa cutoff and of 4e-6 of the
+// terms' sizes, which is above the rounding of these bounds and of the exponents
+// that the per-voxel test compares (in needles the terms cancel, and the first
+// margin alone is not), so every voxel keeps the decision of that test.
 
 // Tiles per Gaussian and pairs per tile from which interior quarters (forward)
 // and pairs (backward) are evaluated by products along the row. They change the
@@ -635,6 +637,7 @@ struct TilePoly {
   float a00, a10, a01, e0;
   float g[3];  // gradient at the centre
   float q;     // value at the centre
+  float err;   // bound on the rounding of the form's values over the tile
 };
 
 __device__ __forceinline__ TilePoly tile_poly(const float4 &p, const float4 &c0, const float4 &c1, float ox, float oy,
@@ -647,6 +650,9 @@ __device__ __forceinline__ TilePoly tile_poly(const float4 &p, const float4 &c0,
   T.g[1] = fmaf(c0.y, dx, fmaf(2.f * c0.w, dy, c1.x * dz));
   T.g[2] = fmaf(c0.z, dx, fmaf(c1.x, dy, 2.f * c1.y * dz));
   const float h = 0.5f * (kVT - 1);
+  const float size = fabsf(c0.x) + fabsf(c0.y) + fabsf(c0.z) + fabsf(c0.w) + fabsf(c1.x) + fabsf(c1.y);
+  const float far = fmaxf(fmaxf(fabsf(dx), fabsf(dy)), fabsf(dz)) + h;
+  T.err = 4e-6f * size * far * far;
   T.a00 = fmaf(h * h, c0.x, fmaf(-h, T.g[0], T.q));
   T.a10 = fmaf(-h, c0.y, T.g[1]);
   T.a01 = fmaf(-h, c0.z, T.g[2]);
@@ -669,8 +675,8 @@ __device__ __forceinline__ void quarter_masks(const TilePoly &T, const float4 &c
     const float gz = fmaf(c1.x, Y, fmaf(2.f * c1.y, Z, T.g[2]));
     const float q = fmaf(Y, fmaf(c0.w, Y, fmaf(c1.x, Z, T.g[1])), fmaf(Z, fmaf(c1.y, Z, T.g[2]), T.q));
     const float slope = fmaf(3.5f, fabsf(gx), 1.5f * (fabsf(gy) + fabsf(gz)));
-    if (!(q + slope < thr_cull)) reach |= 1u << Q;
-    if (q - slope - drop >= thr_int) inner |= 1u << Q;
+    if (!(q + slope < thr_cull - T.err)) reach |= 1u << Q;
+    if (q - slope - drop >= thr_int + T.err) inner |= 1u << Q;
   }
   // the products along a row stay far from the ends of FP32's range: their
   // exponent is at most |threshold| + 49 |c|
@@ -1302,7 +1308,7 @@ __global__ __launch_bounds__(kWave * TPB) __attribute__((amdgpu_waves_per_eu(5, 
       const float slope = h * (fabsf(T.g[0]) + fabsf(T.g[1]) + fabsf(T.g[2]));
       const float drop = h * h * (fabsf(c0.x) + fabsf(c0.y) + fabsf(c0.z) + fabsf(c0.w) + fabsf(c1.x) + fabsf(c1.y));
       have = true;
-      inside = T.q - slope - drop >= c1.z - thr_widen && c1.z > -64.f && c0.x > -0.75f;
+      inside = T.q - slope - drop >= c1.z - thr_widen + T.err && c1.z > -64.f && c0.x > -0.75f;
     }
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
