@@ -325,9 +325,25 @@ __device__ __forceinline__ void chunk_hits(const Rect3 &rc, uint32_t j0, uint32_
 // Gaussian, 75 us now).
 constexpr int kWaveGauss = 4;
 constexpr uint32_t kSmallTiles = 64;
+// Below this many Gaussians a wave takes one, by the code for large
+// rectangles: four, one after the other, leave SIMDs without a wave. Count and
+// emission at 256^3, four and one per wave: 2,000 Gaussians of sigma 15 voxels 121 + 181
+// and 89 + 129 us, 700 of 25 voxels 208 + 320 and 108 + 167; 16,000 of 5 voxels 19.6 + 15.5
+// and 15.5 + 13.2, of 1.5 voxels 6.4 + 6.3 and 11.6 + 7.7.
+constexpr uint64_t kFewGauss = 16384;
+
+// Calls f(std::integral_constant<int, Gaussians per wave>).
+template <typename F>
+void with_wave_gauss(uint64_t n, F &&f) {
+  if (n < kFewGauss)
+    f(std::integral_constant<int, 1>());
+  else
+    f(std::integral_constant<int, kWaveGauss>());
+}
 
 // The number of tiles of each Gaussian's rectangle that its support reaches
 // (the key count).
+template <int PER>
 __global__ __launch_bounds__(256) void vox_count_kernel(int64_t n, const float4 *__restrict__ prho,
                                                         const float4 *__restrict__ a0,
                                                         const float4 *__restrict__ a1,
@@ -337,10 +353,10 @@ __global__ __launch_bounds__(256) void vox_count_kernel(int64_t n, const float4 
   __shared__ unsigned long long s_words[4][kHitWords];
   __shared__ unsigned short s_unsure[4][kHitTiles];
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t i0 = (int64_t(blockIdx.x) * 4 + wid) * kWaveGauss;
+  const int64_t i0 = (int64_t(blockIdx.x) * 4 + wid) * PER;
   if (i0 >= n) return;
   const int grp = lane >> 4, l16 = lane & 15;
-  {
+  if (PER > 1) {
     const int64_t i = i0 + grp;
     Rect3 rc{};
     uint32_t nt = 0;
@@ -374,12 +390,12 @@ __global__ __launch_bounds__(256) void vox_count_kernel(int64_t n, const float4 
       count[i] = uint32_t(__popcll(word));
     }
   }
-  for (int g = 0; g < kWaveGauss; ++g) {
+  for (int g = 0; g < PER; ++g) {
     const int64_t i = i0 + g;
     if (i >= n) break;
     const Rect3 rc = rect[i];
     const uint32_t nt = rect_tiles(rc);
-    if (nt <= kSmallTiles) continue;
+    if (PER > 1 && nt <= kSmallTiles) continue;
     uint32_t cnt = 0;
     const float4 p = prho[i], c0 = a0[i], c1 = a1[i];
     for (uint32_t j0 = 0; j0 < nt; j0 += kHitTiles) {
@@ -401,6 +417,7 @@ __global__ __launch_bounds__(256) void vox_count_kernel(int64_t n, const float4 
 // order, at its offset. The sort's value is the emission slot q (a Gaussian's
 // slots are contiguous, which is where the backward writes its partial sums);
 // gid[q] is the Gaussian.
+template <int PER>
 __global__ __launch_bounds__(256) void vox_emit_kernel(int64_t n, int ntx, int nty, const float4 *__restrict__ prho,
                                                        const float4 *__restrict__ a0,
                                                        const float4 *__restrict__ a1,
@@ -414,7 +431,7 @@ __global__ __launch_bounds__(256) void vox_emit_kernel(int64_t n, int ntx, int n
   __shared__ unsigned long long s_words[4][kHitWords];
   __shared__ unsigned short s_unsure[4][kHitTiles];
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t i0 = (int64_t(blockIdx.x) * 4 + wid) * kWaveGauss;
+  const int64_t i0 = (int64_t(blockIdx.x) * 4 + wid) * PER;
   if (i0 >= n) return;
   const int grp = lane >> 4, l16 = lane & 15;
   auto put = [&](uint32_t q, uint32_t tx, uint32_t ty, uint32_t tz, int64_t i) {
@@ -422,7 +439,7 @@ __global__ __launch_bounds__(256) void vox_emit_kernel(int64_t n, int ntx, int n
     vals[q] = q;
     gid[q] = uint32_t(i);
   };
-  {
+  if (PER > 1) {
     const int64_t i = i0 + grp;
     unsigned long long word = 0;
     uint32_t o = 0;
@@ -444,14 +461,14 @@ __global__ __launch_bounds__(256) void vox_emit_kernel(int64_t n, int ntx, int n
       if (r == 48) break;
     }
   }
-  for (int g = 0; g < kWaveGauss; ++g) {
+  for (int g = 0; g < PER; ++g) {
     const int64_t i = i0 + g;
     if (i >= n) break;
     uint32_t o = offset[i];
     if (o == offset[i + 1]) continue;
     const Rect3 rc = rect[i];
     const uint32_t nt = rect_tiles(rc);
-    if (nt <= kSmallTiles) continue;
+    if (PER > 1 && nt <= kSmallTiles) continue;
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     const bool stored = nt <= uint32_t(kHitTiles);  // the count kept this rectangle's ballots
     TileWalk w(rc, uint32_t(lane));
@@ -1590,9 +1607,13 @@ int vox_build(const fgs_gaussians *g, const fgs_grid *grid, const fgs_opts *o, f
                                                       at<Rect3>(b, L.rect));
   FGS_LAUNCH_CHECK("vox_record_kernel");
   const float thr_widen = cull_widening(o);
-  vox_count_kernel<<<grid_for(N, 4 * kWaveGauss), 256, 0, s>>>(int64_t(N), at<float4>(b, L.prho), at<float4>(b, L.a0),
-                                                   at<float4>(b, L.a1), at<Rect3>(b, L.rect), thr_widen,
-                                                   at<uint32_t>(b, L.offset), at<unsigned long long>(b, L.hits));
+  with_wave_gauss(N, [&](auto per) {
+    constexpr int PER = decltype(per)::value;
+    vox_count_kernel<PER><<<grid_for(N, 4 * PER), 256, 0, s>>>(int64_t(N), at<float4>(b, L.prho), at<float4>(b, L.a0),
+                                                               at<float4>(b, L.a1), at<Rect3>(b, L.rect), thr_widen,
+                                                               at<uint32_t>(b, L.offset),
+                                                               at<unsigned long long>(b, L.hits));
+  });
   FGS_LAUNCH_CHECK("vox_count_kernel");
   // offsets, the 64-bit pair total and the device pair count (0 past the
   // capacity) in one scan
@@ -1616,11 +1637,13 @@ int vox_build(const fgs_gaussians *g, const fgs_grid *grid, const fgs_opts *o, f
   }
   const uint64_t K = L.K;
   if (K > 0) {
-    vox_emit_kernel<<<grid_for(N, 4 * kWaveGauss), 256, 0, s>>>(int64_t(N), G.nt[0], G.nt[1], at<float4>(b, L.prho),
-                                                    at<float4>(b, L.a0), at<float4>(b, L.a1), at<Rect3>(b, L.rect),
-                                                    thr_widen, at<uint32_t>(b, L.offset),
-                                                    at<unsigned long long>(b, L.hits), at<uint32_t>(b, L.keys),
-                                                    at<uint32_t>(b, L.vals), at<uint32_t>(b, L.gid), kdev);
+    with_wave_gauss(N, [&](auto per) {
+      constexpr int PER = decltype(per)::value;
+      vox_emit_kernel<PER><<<grid_for(N, 4 * PER), 256, 0, s>>>(
+          int64_t(N), G.nt[0], G.nt[1], at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
+          at<Rect3>(b, L.rect), thr_widen, at<uint32_t>(b, L.offset), at<unsigned long long>(b, L.hits),
+          at<uint32_t>(b, L.keys), at<uint32_t>(b, L.vals), at<uint32_t>(b, L.gid), kdev);
+    });
     FGS_LAUNCH_CHECK("vox_emit_kernel");
   }
   uint32_t *sk, *sv;
