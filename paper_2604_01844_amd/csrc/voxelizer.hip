@@ -533,7 +533,14 @@ __global__ __launch_bounds__(kWave * TPB) void vox_fwd_kernel(const uint32_t *__
   float4 *s_p = s_all[wid][0], *s_a0 = s_all[wid][1], *s_a1 = s_all[wid][2];
   // work unit = (tile, chunk): chunk c takes batches c, c + n_chunks, ... of
   // the tile's list and writes its own partial volume (n_chunks > 1)
-  const uint32_t unit = xcd_block(blockIdx.x, gridDim.x) * TPB + wid;
+  // (whole tiles: runs on a narrow grid, an empty 256^3 76 us against 80; turned on
+  // a wide one, 512^3 with 15 pairs per tile in a body 0.74 ms against 0.99)
+  uint32_t blk;
+  if (n_chunks > 1)
+    blk = xcd_block(blockIdx.x, gridDim.x);
+  else
+    blk = G.nt[0] <= int(kXcds) * 4 ? xcd_run_block(blockIdx.x, gridDim.x) : turned_block(blockIdx.x, gridDim.x);
+  const uint32_t unit = blk * TPB + wid;
   if (unit >= n_tiles * uint32_t(n_chunks)) return;
   const uint32_t tile = unit / uint32_t(n_chunks);
   const uint32_t chunk = unit - tile * uint32_t(n_chunks);
@@ -1519,6 +1526,18 @@ bool longest_first(const fgs_workspace *ws, const VoxLayout &L) {
   return ws->key_capacity == 0 && L.T <= 65536 && L.K >= kWave * L.T && L.K < product_from(L);
 }
 
+// Whether the forward without chunks takes whole tiles as vox_fwd_kernel does:
+// below kShortLists pairs per tile on average there is little to skip, and the
+// lists of quarters cost more than they save (256^3, Gaussians of sigma 3 voxels
+// all over it: 9 pairs per tile 89 us and 98 by quarters, 28 pairs 108 and
+// 112, 42 pairs 150 and 118). Large grids in workgroups of 16 tiles, since most of the
+// time is the volume's writes and the dispatch (an empty 256^3: 76 us, 82 in
+// workgroups of 4). The sums are the same either way.
+constexpr uint64_t kShortLists = 16, kWideBlockTiles = 16384;
+bool short_lists(const fgs_workspace *ws, const VoxLayout &L) {
+  return ws->key_capacity == 0 && L.K < kShortLists * L.T;
+}
+
 // Waves per tile in the backward, whose pairs are independent of each other:
 // as in the forward, but four also where lists average a batch of 64 or
 // more. A wave per tile leaves the longest lists to the end: 200,000 Gaussians
@@ -1738,9 +1757,18 @@ int vox_forward(const fgs_gaussians *g, const fgs_grid *grid, const fgs_opts *op
       tile_order_kernel<<<blocks, 1024, 0, s>>>(at<uint32_t>(b, L.start), uint32_t(L.T), counts, order);
       FGS_LAUNCH_CHECK("tile_order_kernel");
     }
+    auto whole = [&](auto tpb) {
+      constexpr int TPB = decltype(tpb)::value;
+      vox_fwd_kernel<false, TPB><<<grid_for(L.T, TPB), kWave * TPB, 0, s>>>(
+          at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
+          at<uint32_t>(b, L.gid), G, uint32_t(L.T), 1, vol, nullptr);
+    };
     with_vox_pick(
         ws, b, L,
         [&](const VoxPick &pick) {
+          if (short_lists(ws, L) && L.T >= kWideBlockTiles)
+            return whole(std::integral_constant<int, 16>());
+          if (short_lists(ws, L)) return whole(std::integral_constant<int, 4>());
           vox_fwd_ordered_kernel<4><<<grid_for(L.T, 4), kWave * 4, 0, s>>>(
               at<uint32_t>(b, L.start), sv, at<float4>(b, L.prho), at<float4>(b, L.a0), at<float4>(b, L.a1),
               at<uint32_t>(b, L.gid), G, uint32_t(L.T), order, thr_widen, pick, vol);

@@ -1,7 +1,8 @@
 """GPU tests of the voxelizer on grids of 8,192 tiles or more with a fixed key
 capacity, where the kernel (list order, or products along the row) is picked
 on the device: the bits are those of a call that reads its count back, on both
-sides of the line and whatever the capacity. The lists of the product cases
+sides of the line and whatever the capacity, also where that call takes short
+lists by whole tiles. The lists of the product cases
 span several batches of 64, of interior and boundary pairs."""
 import numpy as np
 import pytest
@@ -21,7 +22,9 @@ CASES = [
     (3500, 0.06, 0.3, 0.15, (161, 163, 165), 0.0, True),   # lists of up to 1,000 and more
     (4500, 0.06, 0.3, 0.15, (161, 163, 165), 2e-2, True),
     (500, 0.08, 0.6, 0.2, (2049, 513, 8), 0.0, True),      # one layer of tiles
-    (3000, 0.015, 0.3, 0.3, (161, 163, 165), 0.0, False),
+    (9000, 0.015, 0.3, 0.3, (161, 163, 165), 0.0, False),
+    (3000, 0.015, 0.3, 0.2, (161, 163, 165), 0.0, False),  # fewer than 16 pairs per tile: whole tiles
+    (3000, 0.015, 0.3, 0.2, (209, 208, 211), 0.0, False),  # and 16 tiles per workgroup
 ]
 
 
