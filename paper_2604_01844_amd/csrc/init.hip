@@ -503,8 +503,11 @@ __device__ __forceinline__ void write_scale(float best, float min_dist, int64_t 
   log_scale[2 * n + i] = l;
 }
 
-// Brute force over LDS tiles: for the few calls whose cell arrays do not fit
-// the workspace (many Gaussians drawn from a small grid).
+// Brute force over LDS tiles: for a few points (1,000: 42 us, 60 by cells, most of
+// it launches) and for the few calls whose cell arrays do not fit the
+// workspace (many Gaussians drawn from a small grid).
+constexpr int64_t kFewPoints = 1024;
+
 __global__ __launch_bounds__(256) void nn_scale_kernel(const float *__restrict__ mean, int64_t n,
                                                        float min_dist, float *__restrict__ log_scale) {
   __shared__ float s_p[3][256];
@@ -540,14 +543,17 @@ __global__ __launch_bounds__(256) void nn_scale_kernel(const float *__restrict__
 // the points inside a cell is not fixed, their minimum is: the result is the
 // brute force's, bit for bit. Cells are chosen for four per point: the
 // samples lie on surfaces and fill few of them (a cube of 2 per point holds
-// twice the candidates). Bound by the latency of the candidates' loads.
-// Measured at 50,000 points: 1.58 ms by brute force (196 workgroups, n^2
-// distances), 0.06 ms for the five launches now.
+// twice the candidates). Bound by the latency of the candidates' loads,
+// some 85 ns each: a point that is not decided by the cells up to kMaxRings away
+// (an isolated one), or that would look at more than max_look points (a small
+// object in a wide grid: most points in a few cells), is left to the pass
+// over all points below, whose work does not depend on where the points are.
 struct Cells {
   float o[3], edge, inv;
   int d[3];
 };
 constexpr int kCellsPerPoint = 4;
+constexpr int kMaxRings = 3;
 
 __device__ __forceinline__ int cell_of(const Cells &C, int a, float p) {
   return min(max(int((p - C.o[a]) * C.inv), 0), C.d[a] - 1);
@@ -579,9 +585,12 @@ __global__ __launch_bounds__(256) void cell_fill_kernel(const float *__restrict_
   pts[start[cell_index(C, x, y, z)] + rank[i]] = make_float4(x, y, z, __uint_as_float(uint32_t(i)));
 }
 
+// rest[0 .. rest_n[0]): the points left over; their log_scale holds +infinity,
+// where the pass over all points gathers the squared distance.
 __global__ __launch_bounds__(64) void nn_cells_kernel(const float4 *__restrict__ pts, int64_t n, Cells C,
                                                       const uint32_t *__restrict__ start, float min_dist,
-                                                      float *__restrict__ log_scale) {
+                                                      int max_look, uint32_t *__restrict__ rest_n,
+                                                      uint32_t *__restrict__ rest, float *__restrict__ log_scale) {
   const int64_t q = int64_t(blockIdx.x) * 64 + threadIdx.x;
   if (q >= n) return;
   const float4 p = pts[q];
@@ -589,23 +598,46 @@ __global__ __launch_bounds__(64) void nn_cells_kernel(const float4 *__restrict__
   const int c[3] = {cx, cy, cz};
   const float pc[3] = {p.x, p.y, p.z};
   float best = INFINITY;
-  // cells [x0, x1] of row (y, z): one contiguous piece of pts
-  auto scan = [&](int x0, int x1, int y, int z) {
+  // cells [x0, x1] of row (y, z): one contiguous piece of pts, [a, e)
+  auto row_of = [&](int x0, int x1, int y, int z, uint32_t &a, uint32_t &e) {
     x0 = max(x0, 0);
     x1 = min(x1, C.d[0] - 1);
+    a = e = 0u;
     if (x0 > x1 || y < 0 || y >= C.d[1] || z < 0 || z >= C.d[2]) return;
     const uint32_t row = (uint32_t(z) * uint32_t(C.d[1]) + uint32_t(y)) * uint32_t(C.d[0]);
-    const uint32_t e = start[row + uint32_t(x1) + 1u];
-    for (uint32_t k = start[row + uint32_t(x0)]; k < e; ++k) {
+    a = start[row + uint32_t(x0)];
+    e = start[row + uint32_t(x1) + 1u];
+  };
+  int left = max_look;
+  auto look = [&](uint32_t a, uint32_t e) {
+    if (int(e - a) > left) {
+      left = -1;
+      return;
+    }
+    left -= int(e - a);
+    for (uint32_t k = a; k < e; ++k) {
       const float4 o = pts[k];
       const float d2 = dist2(o.x - p.x, o.y - p.y, o.z - p.z);
       if (k != uint32_t(q)) best = fminf(best, d2);
     }
   };
-  for (int z = -1; z <= 1; ++z)
-    for (int y = -1; y <= 1; ++y) scan(cx - 1, cx + 1, cy + y, cz + z);
-  const int r_max = max(max(C.d[0], C.d[1]), C.d[2]);
-  for (int r = 1; r < r_max;) {
+  auto scan = [&](int x0, int x1, int y, int z) {
+    uint32_t a, e;
+    row_of(x0, x1, y, z, a, e);
+    look(a, e);
+  };
+  // the nine rows around the point's cell, their ends loaded together
+  uint32_t a9[9], e9[9], sum9 = 0;
+#pragma unroll
+  for (int j = 0; j < 9; ++j) {
+    row_of(cx - 1, cx + 1, cy + j % 3 - 1, cz + j / 3 - 1, a9[j], e9[j]);
+    sum9 += e9[j] - a9[j];
+  }
+  if (sum9 > uint32_t(max_look)) left = -1;
+#pragma unroll
+  for (int j = 0; j < 9; ++j) look(a9[j], e9[j]);
+  bool found = false;
+  for (int r = 1;;) {
     // distance to the nearest face of the searched cube that has cells beyond
     // it, less the rounding of a face and of a point's cell
     float face = INFINITY;
@@ -615,7 +647,8 @@ __global__ __launch_bounds__(64) void nn_cells_kernel(const float4 *__restrict__
       if (c[a] - r > 0) face = fminf(face, pc[a] - (C.o[a] + float(c[a] - r) * C.edge) - slack);
       if (c[a] + r < C.d[a] - 1) face = fminf(face, C.o[a] + float(c[a] + r + 1) * C.edge - pc[a] - slack);
     }
-    if (face == INFINITY || (face > 0.f && best <= face * face * 0.9999f)) break;
+    found = left >= 0 && (face == INFINITY || (face > 0.f && best <= face * face * 0.9999f));
+    if (found || left < 0 || r == kMaxRings) break;
     ++r;
     for (int z = -r; z <= r; ++z)
       for (int y = -r; y <= r; ++y) {
@@ -627,7 +660,66 @@ __global__ __launch_bounds__(64) void nn_cells_kernel(const float4 *__restrict__
         }
       }
   }
-  write_scale(best, min_dist, int64_t(__float_as_uint(p.w)), n, log_scale);
+  const int64_t i = int64_t(__float_as_uint(p.w));
+  if (found) write_scale(best, min_dist, i, n, log_scale);
+  const uint64_t more = __ballot(!found);
+  if (!found) {
+    const int lane = threadIdx.x, first = __ffsll(static_cast<unsigned long long>(more)) - 1;
+    uint32_t at = 0;
+    if (lane == first) at = atomicAdd(rest_n, uint32_t(__popcll(more)));
+    at = __shfl(at, first, 64);
+    rest[at + uint32_t(__popcll(more & ((1ull << lane) - 1ull)))] = uint32_t(q);
+    log_scale[i] = INFINITY;
+  }
+}
+
+// The points left over against all n: an item is 256 of them and kRestSeg
+// others, staged in LDS, so that a few points' work is spread too; the pieces
+// meet in log_scale by an atomic minimum over the bits (squares are not
+// negative), which no order changes. 50,000 points all left over: 2.5 G
+// distances.
+constexpr int kRestSeg = 2048;
+
+__global__ __launch_bounds__(256) void nn_rest_kernel(const float4 *__restrict__ pts, int64_t n,
+                                                      const uint32_t *__restrict__ rest_n,
+                                                      const uint32_t *__restrict__ rest,
+                                                      float *__restrict__ log_scale) {
+  __shared__ float4 s_p[256];
+  const uint32_t m = rest_n[0], groups = (m + 255u) / 256u;
+  const uint32_t segs = uint32_t((n + kRestSeg - 1) / kRestSeg);
+  for (uint64_t item = blockIdx.x; item < uint64_t(groups) * segs; item += gridDim.x) {
+    const uint32_t g = uint32_t(item / segs), sg = uint32_t(item - uint64_t(g) * segs);
+    const uint32_t j = g * 256u + threadIdx.x;
+    const bool mine = j < m;
+    const uint32_t q = mine ? rest[j] : 0u;
+    const float4 p = pts[q];
+    float best = INFINITY;
+    const int64_t k0 = int64_t(sg) * kRestSeg, k1 = min(n, k0 + kRestSeg);
+    for (int64_t base = k0; base < k1; base += 256) {
+      __syncthreads();
+      if (base + threadIdx.x < k1) s_p[threadIdx.x] = pts[base + threadIdx.x];
+      __syncthreads();
+      const int cnt = int(min(int64_t(256), k1 - base));
+      const int own = int(int64_t(q) - base);  // the point itself, if it is in this tile
+#pragma unroll 4
+      for (int t = 0; t < cnt; ++t) {
+        const float4 o = s_p[t];
+        const float d2 = dist2(o.x - p.x, o.y - p.y, o.z - p.z);
+        best = t != own ? fminf(best, d2) : best;
+      }
+    }
+    if (mine) atomicMin(reinterpret_cast<unsigned int *>(log_scale) + __float_as_uint(p.w), __float_as_uint(best));
+  }
+}
+
+__global__ __launch_bounds__(256) void nn_rest_scale_kernel(const float4 *__restrict__ pts, int64_t n,
+                                                            const uint32_t *__restrict__ rest_n,
+                                                            const uint32_t *__restrict__ rest, float min_dist,
+                                                            float *__restrict__ log_scale) {
+  for (uint32_t j = blockIdx.x * 256u + threadIdx.x; j < rest_n[0]; j += gridDim.x * 256u) {
+    const int64_t i = int64_t(__float_as_uint(pts[rest[j]].w));
+    write_scale(log_scale[i], min_dist, i, n, log_scale);
+  }
 }
 
 // Cells of a box of the given extents holding about kCellsPerPoint n of them.
@@ -772,11 +864,11 @@ static int sampling_init(Weighting mode, const float *vol, const fgs_grid *grid,
   const uint64_t nc = uint64_t(C.d[0]) * C.d[1] * C.d[2];
   Carver cc(nullptr);
   uint64_t o_cell, o_rank, o_pts, o_cscan;
-  cc.take<uint32_t>(nc + 1, &o_cell);
+  cc.take<uint32_t>(nc + 2, &o_cell);  // the last word: the number of points left over
   cc.take<uint32_t>(uint64_t(n), &o_rank);
   cc.take<float4>(uint64_t(n), &o_pts);
   cc.take<uint32_t>(scan_scratch_words(nc), &o_cscan);
-  if (o_g + cc.used > c.used || n > 0x7fffffff || nc > 0x7fffffff) {
+  if (n <= kFewPoints || o_g + cc.used > c.used || n > 0x7fffffff || nc > 0x7fffffff) {
     nn_scale_kernel<<<grid_for(uint64_t(n), 256), 256, 0, s>>>(out->mean, n, min_scale, out->log_scale);
     FGS_LAUNCH_CHECK("nn_scale_kernel");
     return FGS_OK;
@@ -785,15 +877,24 @@ static int sampling_init(Weighting mode, const float *vol, const fgs_grid *grid,
   uint32_t *cell = reinterpret_cast<uint32_t *>(r + o_cell), *rank = reinterpret_cast<uint32_t *>(r + o_rank);
   float4 *pts = reinterpret_cast<float4 *>(r + o_pts);
   const unsigned nb_n = grid_for(uint64_t(n), 256);
-  cell_zero_kernel<<<grid_for(nc, 256), 256, 0, s>>>(cell, uint32_t(nc));
+  cell_zero_kernel<<<grid_for(nc + 2, 256), 256, 0, s>>>(cell, uint32_t(nc + 2));
   cell_count_kernel<<<nb_n, 256, 0, s>>>(out->mean, n, C, cell, rank);
   FGS_LAUNCH_CHECK("cell_count_kernel");
   st = exclusive_scan_u32(cell, nc, reinterpret_cast<uint32_t *>(r + o_cscan), s);
   if (st != FGS_OK) return st;
   cell_fill_kernel<<<nb_n, 256, 0, s>>>(out->mean, n, C, cell, rank, pts);
   FGS_LAUNCH_CHECK("cell_fill_kernel");
-  nn_cells_kernel<<<grid_for(uint64_t(n), 64), 64, 0, s>>>(pts, n, C, cell, min_scale, out->log_scale);
+  // the ranks are done with: their room holds the points left over
+  uint32_t *rest = rank, *rest_n = cell + nc + 1;
+  const int max_look = int(std::max<int64_t>(256, n / 16));
+  nn_cells_kernel<<<grid_for(uint64_t(n), 64), 64, 0, s>>>(pts, n, C, cell, min_scale, max_look, rest_n, rest,
+                                                           out->log_scale);
   FGS_LAUNCH_CHECK("nn_cells_kernel");
+  const uint64_t items = uint64_t(nb_n) * grid_for(uint64_t(n), kRestSeg);
+  nn_rest_kernel<<<unsigned(std::min<uint64_t>(2048, items)), 256, 0, s>>>(pts, n, rest_n, rest, out->log_scale);
+  FGS_LAUNCH_CHECK("nn_rest_kernel");
+  nn_rest_scale_kernel<<<std::min(256u, nb_n), 256, 0, s>>>(pts, n, rest_n, rest, min_scale, out->log_scale);
+  FGS_LAUNCH_CHECK("nn_rest_scale_kernel");
   return FGS_OK;
 }
 
