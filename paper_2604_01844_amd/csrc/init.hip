@@ -332,6 +332,51 @@ __global__ __launch_bounds__(256) void fdk_backproject_kernel(FdkGeom G, const f
   }
 }
 
+// A voxel per thread, sampled from global memory, with the arithmetic of the
+// kernel above.
+__global__ __launch_bounds__(256) void fdk_voxel_kernel(FdkGeom G, const float *__restrict__ q,
+                                                        float *__restrict__ vol) {
+  __shared__ float s_cs[1024][2];
+  for (int v = threadIdx.x; v < G.views; v += 256) {
+    float sn, cs;
+    sincosf(G.angles[G.view_begin + v], &sn, &cs);
+    s_cs[v][0] = cs;
+    s_cs[v][1] = sn;
+  }
+  __syncthreads();
+  const int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  const int64_t nxy = int64_t(G.dims[0]) * G.dims[1];
+  if (idx >= nxy * G.dims[2]) return;
+  const int iz = int(idx / nxy), ixy = int(idx - iz * nxy), iy = ixy / G.dims[0], ix = ixy - iy * G.dims[0];
+  auto centre = [&](int a, int i) { return G.origin[a] + (float(i) + 0.5f) * G.h[a]; };
+  const float x = centre(0, ix), y = centre(1, iy), z = centre(2, iz);
+  const float cuh = G.cu - 0.5f, cvh = G.cv - 0.5f;
+  float acc = 0.f;
+  for (int v = 0; v < G.views; ++v) {
+    const float c = s_cs[v][0], s = s_cs[v][1];
+    const float dx = x - G.sod * c, dy = y - G.sod * s;
+    const float t0 = -s * dx + c * dy;
+    const float t2 = -c * dx - s * dy;
+    if (!(t2 > 0.f)) continue;
+    const float it = 1.f / t2;
+    const float u = fmaf(G.fu * t0, it, cuh), w = fmaf(-G.fv * z, it, cvh);
+    const float u0f = floorf(u), w0f = floorf(w);
+    const int u0 = int(u0f), w0 = int(w0f);
+    const float fu = u - u0f, gu = 1.f - fu, fw = w - w0f;
+    const float wt = G.sod * it, wt2 = wt * wt;
+    const float *qv = q + uint64_t(v) * (uint64_t(G.H) * uint64_t(G.W));
+    auto at = [&](uint32_t du, uint32_t dw) -> float {
+      return index_inside(u0, du, G.W) && index_inside(w0, dw, G.H)
+                 ? qv[uint64_t(uint32_t(w0) + dw) * G.W + (uint32_t(u0) + du)]
+                 : 0.f;
+    };
+    const float top = fmaf(fu, at(1, 0), gu * at(0, 0));
+    const float bot = fmaf(fu, at(1, 1), gu * at(0, 1));
+    acc = fmaf(wt2, fmaf(fw, bot, (1.f - fw) * top), acc);
+  }
+  vol[idx] = G.scale * acc;
+}
+
 // ------------------------------------------------------------ init sampling
 
 constexpr int kRedThreads = 256;
@@ -503,7 +548,7 @@ __device__ __forceinline__ void write_scale(float best, float min_dist, int64_t 
   log_scale[2 * n + i] = l;
 }
 
-// Brute force over LDS tiles: for a few points (1,000: 42 us, 60 by cells, most of
+// Brute force over LDS tiles: for a few points (1,000: 33 us, 53 by cells, most of
 // it launches) and for the few calls whose cell arrays do not fit the
 // workspace (many Gaussians drawn from a small grid).
 constexpr int64_t kFewPoints = 1024;
@@ -548,6 +593,10 @@ __global__ __launch_bounds__(256) void nn_scale_kernel(const float *__restrict__
 // (an isolated one), or that would look at more than max_look points (a small
 // object in a wide grid: most points in a few cells), is left to the pass
 // over all points below, whose work does not depend on where the points are.
+// Measured at 50,000 points: 1.58 ms by brute force (196 workgroups, n^2
+// distances), 0.07 ms for the seven launches where they lie on surfaces; the
+// whole placement with all of them around one voxel 1.88 ms by brute force,
+// 7.3 by cells alone, 1.42 now; 5,000, some of them isolated, 0.45, 0.90 and 0.41.
 struct Cells {
   float o[3], edge, inv;
   int d[3];
@@ -737,6 +786,19 @@ Cells make_cells(const float o[3], const double extent[3], int64_t n) {
   return C;
 }
 
+// Whether a grid is backprojected from staged pieces: enough voxels for the
+// chip, and not too many lost to the padding of its columns and runs. 75 views,
+// backprojection by a voxel per thread and from pieces: 256^2 to 64^3 67 and 154 us, 160^2 to
+// 80^3 100 and 96, 192^2 to 96^3 162 and 134; 512^2 to slices of 512 x 512: one 47 and 126,
+// three 106 and 124, eight 250 and 227; 512^2 to 256^3 (runs of 16) 2,605 and 801.
+constexpr uint64_t kFdkStagedVoxels = uint64_t(1) << 19;
+bool fdk_staged(const FdkGeom &G, int run) {
+  const uint64_t nxy = uint64_t(G.dims[0]) * G.dims[1], n = nxy * G.dims[2];
+  auto up = [](uint64_t d, uint64_t m) { return (d + m - 1) / m * m; };
+  const uint64_t padded = up(G.dims[0], 16) * up(G.dims[1], 16) * up(G.dims[2], run);
+  return n >= kFdkStagedVoxels && 4 * padded <= (run == 16 ? 12 : 5) * n;
+}
+
 }  // namespace
 }  // namespace fgs
 
@@ -787,11 +849,13 @@ extern "C" int fgs_fdk(const float *img, const fgs_geom *geom, int32_t view_begi
   G.blocks_x = (grid->dims[0] + 15) / 16;
   const dim3 bgrid(unsigned(G.blocks_x) * unsigned((grid->dims[1] + 15) / 16),
                    std::min(65535u, grid_for(uint64_t(grid->dims[2]), lng ? 16 : 4)));
-  if (lng)
+  if (!fdk_staged(G, lng ? 16 : 4))
+    fdk_voxel_kernel<<<grid_for(nxy * uint64_t(grid->dims[2]), 256), 256, 0, s>>>(G, q, vol);
+  else if (lng)
     fdk_backproject_kernel<16><<<bgrid, 256, 0, s>>>(G, q, vol);
   else
     fdk_backproject_kernel<4><<<bgrid, 256, 0, s>>>(G, q, vol);
-  FGS_LAUNCH_CHECK("fdk_backproject_kernel");
+  FGS_LAUNCH_CHECK("fdk_backproject_kernel / fdk_voxel_kernel");
   return FGS_OK;
 }
 

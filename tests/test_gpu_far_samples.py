@@ -38,7 +38,7 @@ def test_patch_of_a_far_mean_is_zero():
     assert torch.equal(x[:, 512:515], (2 * mean.T).to(torch.bfloat16))
 
 
-@pytest.mark.parametrize("dims", [(17, 17, 17), (165, 161, 161)])  # runs of 4 and of 16 voxels
+@pytest.mark.parametrize("dims", [(17, 17, 17), (96, 97, 63), (165, 161, 161)])  # one voxel, runs of 4, of 16
 def test_fdk_voxels_beside_the_source(dims):
     """A plane of voxels 2^-25 in front of the source, whose rays meet the
     detector's plane up to 2^31 pixels away, and voxels behind the source. A
