@@ -103,8 +103,10 @@ __global__ __launch_bounds__(512) void fdk_filter_kernel(const float *__restrict
     const float *tap = &s_tap[at + l32 - lh + par + kFilterHalf - 1];
     if (2 * (A0 + at) + par < W) {
       // pieces of kFilterPiece products, each summed by itself and then added:
-      // shorter chains of roundings than one running sum
-      for (int b0 = 0; b0 < kFilterHalf; b0 += kFilterPiece) {
+      // shorter chains of roundings than one running sum; those past the row's
+      // end hold zeros (75 views of 32^2: 19.6 us with them)
+      const int b_end = min(kFilterHalf, (W - j0 + 1) / 2);
+      for (int b0 = 0; b0 < b_end; b0 += kFilterPiece) {
         f32x16 p0 = {0.f}, p1 = {0.f};
 #pragma unroll
         for (int b = b0; b < b0 + kFilterPiece; b += 2) {
