@@ -75,7 +75,10 @@ __global__ __launch_bounds__(512) void fdk_filter_kernel(const float *__restrict
     {
       const int d = d0 + int(threadIdx.x);
       const float m = float(2 * d - 1);
-      s_tap[threadIdx.x] = fabsf(m) > 1.f ? -inv / (pi2 * m * m) : 0.f;  // the neighbours' taps: below
+      // The neighbours' taps come below; not zero here, so that an infinite
+      // sample adds its infinity to the neighbours and not a NaN (a finite one
+      // adds nothing that its own tap's 1e-38th part would show).
+      s_tap[threadIdx.x] = fabsf(m) > 1.f ? -inv / (pi2 * m * m) : -1e-37f;
     }
     const int j = j0 + int(threadIdx.x);
     const float a = (float(j) + 0.5f - cu) * pu;
