@@ -1528,36 +1528,75 @@ struct ExactCam {
 };
 
 // Four waves share a tile (or, with few tiles, each of its chunks): they take
-// the batches of its list in turn. Lists are uneven (50,000 Gaussians of sigma
+// the batches of its list in turn, where lists are long enough. Lists are uneven (50,000 Gaussians of sigma
 // 0.03 at 512 x 512: up to some 2,000 in the body's tiles, none around it) and
 // these kernels issue little else than arithmetic, so with a wave per list the
 // longest ones and the CUs that held them ended last: CUs busy 44% (forward) and 59%
 // (backward) of the time over 4 views; forward and backward with their binning
-// 1.67 -> 1.09 ms, over 16 views 5.3 -> 3.7 ms.
+// 1.67 -> 1.09 ms, over 16 views 5.3 -> 3.7 ms. Short lists leave three of the four
+// without a batch, the more of the time the more tiles there are: one wave
+// and four, detectors of 512 x 512, 75 views: 6 keys per tile 0.69 and 0.83 ms, 84
+// keys 2.15 and 2.22, 164 keys 3.48 and 3.35; 16 views, 84 keys 0.66 and 0.57. So four from a
+// mean length of T / 512 keys on, 128 where there are 65,536 tiles or more (as
+// share_rule).
 constexpr int kExactWaves = 4;
+enum ShareMode { kOwnTiles, kSharedTiles, kSharedByCount };
+inline Share exact_share_rule(uint64_t T, int chunks, uint64_t K, bool capacity) {
+  if (chunks > 1) return {kShareAlways, 0};
+  const uint64_t from = T * (T < 65536 ? T : 65536) / 512;
+  if (capacity) return {from, 0};
+  return {K >= from ? kShareAlways : kShareNever, 0};
+}
 
-// Blocks of the ray-exact kernels; rows of blocks keep the work-items of each
-// dimension below 2^32.
-inline dim3 exact_blocks(uint64_t units) {
+// Calls f(std::integral_constant<ShareMode, mode>): known to the compiler, since a
+// choice at run time costs the kernels 1-2%.
+template <typename F>
+void with_share(const Share &share, F &&f) {
+  if (share.from == kShareNever)
+    f(std::integral_constant<ShareMode, kOwnTiles>());
+  else if (share.from == kShareAlways)
+    f(std::integral_constant<ShareMode, kSharedTiles>());
+  else
+    f(std::integral_constant<ShareMode, kSharedByCount>());
+}
+
+// Blocks of the ray-exact kernels, at most one per unit; rows of blocks keep
+// the work-items of each dimension below 2^32.
+inline dim3 exact_blocks(uint64_t units, const Share &share) {
   constexpr uint64_t kRow = 1u << 22;
-  return units <= kRow ? dim3(unsigned(units)) : dim3(unsigned(kRow), grid_for(units, unsigned(kRow)));
+  const uint64_t n = share.from == kShareNever ? (units + kExactWaves - 1) / kExactWaves : units;
+  return n <= kRow ? dim3(unsigned(n)) : dim3(unsigned(kRow), grid_for(n, unsigned(kRow)));
 }
-// Their order: from four views on each XCD takes an eighth of the tiles, half
-// a view or more, and its L2 keeps their records (8 views of 600 x 600: 2.50 ms, 2.72 in
-// the natural order); below that an eighth is a few rows of one view, empty
-// for the outer XCDs, and the natural order shares the work (1 view of 512 x 512: 0.39 ms,
-// 0.54 by eighths; 2 of 256 x 256: 0.30 and 0.38).
-__device__ __forceinline__ uint64_t exact_unit(uint32_t views) {
-  return uint64_t(blockIdx.y) * gridDim.x +
-         (views >= 4 ? xcd_turned_block(blockIdx.x, gridDim.x) : turned_block(blockIdx.x, gridDim.x));
+// The unit (tile and chunk) of this wave and its first batch; false past the
+// last. Order of the blocks: from four views on each XCD takes an eighth of the
+// tiles, half a view or more, and its L2 keeps their records (8 views of 600 x 600:
+// 2.50 ms, 2.72 in the natural order); below that an eighth is a few rows of one view,
+// empty for the outer XCDs, and the natural order shares the work (1 view of 512 x 512:
+// 0.39 ms, 0.54 by eighths; 2 of 256 x 256: 0.30 and 0.38).
+template <ShareMode kShare>
+__device__ __forceinline__ bool exact_unit(uint64_t share_from, const uint32_t *kdev, uint32_t n_tiles, uint32_t n_chunks,
+                                           uint32_t views, int wid, bool &share, uint32_t &unit, uint32_t &batch) {
+  share = kShare == kSharedTiles || (kShare == kSharedByCount && kdev[0] >= share_from);
+  const uint64_t units = uint64_t(n_tiles) * n_chunks, row = uint64_t(blockIdx.y) * gridDim.x;
+  const uint64_t nb = share ? units : (units + kExactWaves - 1) / kExactWaves;
+  // (a shared launch holds as many blocks as there are, but for its last row's rest)
+  uint32_t len = gridDim.x;
+  if (kShare != kSharedTiles) {
+    if (row + blockIdx.x >= nb) return false;
+    len = uint32_t(min(uint64_t(len), nb - row));
+  }
+  const uint64_t b = row + (views >= 4 ? xcd_turned_block(blockIdx.x, len) : turned_block(blockIdx.x, len));
+  batch = share ? uint32_t(wid) : 0u;
+  unit = share ? uint32_t(b) : uint32_t(b) * kExactWaves + uint32_t(wid);
+  return share ? b < units : unit < units;
 }
 
-// The waves' sums meet in LDS in a fixed order; wave k writes pixel row k.
-template <bool kCount>
+// Shared: the waves' sums meet in LDS in a fixed order; wave k writes pixel row k.
+template <bool kCount, ShareMode kShare>
 __global__ __launch_bounds__(kWave * kExactWaves) void splat_fwd_exact_kernel(
     const uint2 *__restrict__ rng, const ListRecs svals, const ExactRec *__restrict__ rec,
-    int tiles_x, int tpv, int W, int H, uint32_t n_tiles, int n_chunks, float thr, float thr_cull, ExactCam cam,
-    float *__restrict__ img, unsigned long long *__restrict__ counter) {
+    const uint32_t *__restrict__ kdev, uint64_t share_from, int tiles_x, int tpv, int W, int H, uint32_t n_tiles,
+    int n_chunks, float thr, float thr_cull, ExactCam cam, float *__restrict__ img, unsigned long long *__restrict__ counter) {
   __shared__ float4 s_a_all[kExactWaves][kWave + 1];
   __shared__ float4 s_b_all[kExactWaves][kWave + 1];
   __shared__ float4 s_c_all[kExactWaves][kWave + 1];
@@ -1570,9 +1609,11 @@ __global__ __launch_bounds__(kWave * kExactWaves) void splat_fwd_exact_kernel(
   float4 *s_c = s_c_all[wid];
   float *s_w = s_w_all[wid];
   uint8_t(*s_list)[kWave] = s_list_all[wid];
-  const uint64_t block = exact_unit(n_tiles / uint32_t(tpv));
-  if (block >= uint64_t(n_tiles) * uint32_t(n_chunks)) return;
-  const uint32_t unit = uint32_t(block);
+  bool share;
+  uint32_t unit, batch;
+  if (!exact_unit<kShare>(share_from, kdev, n_tiles, uint32_t(n_chunks), n_tiles / uint32_t(tpv), wid, share, unit, batch))
+    return;
+  const uint32_t per = share ? kExactWaves : 1;  // waves of a unit
   const uint32_t tile = unit / uint32_t(n_chunks);
   const uint32_t chunk = unit - tile * uint32_t(n_chunks);
   const uint32_t v_local = tile / uint32_t(tpv);
@@ -1596,8 +1637,8 @@ __global__ __launch_bounds__(kWave * kExactWaves) void splat_fwd_exact_kernel(
 #pragma unroll
   for (int k = 0; k < kRows; ++k) acc[k] = 0.f;
   const uint32_t b0 = rng[rt].x, e = rng[rt].y;
-  const uint32_t step = uint32_t(kWave * kExactWaves) * uint32_t(n_chunks);
-  for (uint32_t b = b0 + (chunk * kExactWaves + wid) * kWave; b < e; b += step) {
+  const uint32_t step = kWave * per * uint32_t(n_chunks);
+  for (uint32_t b = b0 + (chunk * per + batch) * kWave; b < e; b += step) {
     const uint32_t m = min(uint32_t(kWave), e - b);
     uint32_t mask = 0;
     if (uint32_t(lane) < m) {
@@ -1657,6 +1698,15 @@ __global__ __launch_bounds__(kWave * kExactWaves) void splat_fwd_exact_kernel(
     return;
   }
   float *out = img + (uint64_t(chunk) * (n_tiles / uint32_t(tpv)) + v_local) * uint64_t(W) * uint64_t(H);
+  if (!share) {
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) {
+      const int y = ty * kTS + row0 + k;
+      if (x < W && y < H)
+        out[uint64_t(y) * W + x] = acc[k] * ray_length(px, py + float(k), cam.fu, cam.fv, cam.cu, cam.cv);
+    }
+    return;
+  }
   static_assert(kExactWaves == kRows, "wave k sums and writes row k");
 #pragma unroll
   for (int k = 0; k < kRows; ++k) s_acc[wid][k][lane] = acc[k];
@@ -1680,10 +1730,11 @@ constexpr int kExactSums = 13;
 // then moved to the Gaussian's centre. With p = g |d| A^-1/2 exp(phi) the
 // sums are those exact_backward takes: sum p, sum p C / A, and the moments
 // of alpha = -(p / A)(1/2 + phi) and beta = p / A.
+template <ShareMode kShare>
 __global__ __launch_bounds__(kWave * kExactWaves) void splat_bwd_exact_kernel(
     const uint2 *__restrict__ rng, const ListRecs svals, const ExactRec *__restrict__ rec,
-    int tiles_x, int tpv, int W, int H, uint32_t n_tiles, int n_chunks, float thr, float thr_cull, ExactCam cam,
-    const float *__restrict__ gimg, float4 *__restrict__ partials) {
+    const uint32_t *__restrict__ kdev, uint64_t share_from, int tiles_x, int tpv, int W, int H, uint32_t n_tiles,
+    int n_chunks, float thr, float thr_cull, ExactCam cam, const float *__restrict__ gimg, float4 *__restrict__ partials) {
   __shared__ float4 s_g4_all[kExactWaves][kTS * kTS / 4];
   __shared__ float4 s_a_all[kExactWaves][kWave + 1];
   __shared__ float4 s_b_all[kExactWaves][kWave + 1];
@@ -1696,11 +1747,14 @@ __global__ __launch_bounds__(kWave * kExactWaves) void splat_bwd_exact_kernel(
   float4 *s_b = s_b_all[wid];
   float4 *s_c = s_c_all[wid];
   uint8_t *s_cat = s_cat_all[wid];
-  const uint64_t block = exact_unit(n_tiles / uint32_t(tpv));
-  if (block >= uint64_t(n_tiles) * uint32_t(n_chunks)) return;
-  const uint32_t unit = (uint32_t(block) * kExactWaves + wid) / kExactWaves;  // per lane: 10 us less than in scalars
+  bool share;
+  uint32_t unit, batch;
+  if (!exact_unit<kShare>(share_from, kdev, n_tiles, uint32_t(n_chunks), n_tiles / uint32_t(tpv), wid, share, unit, batch))
+    return;
+  const uint32_t per = share ? kExactWaves : 1;  // waves of a unit
+  if (kShare == kSharedTiles) unit = (unit * kExactWaves + wid) / kExactWaves;  // per lane: 10 us less than in scalars
   const uint32_t tile = unit / uint32_t(n_chunks);
-  const uint32_t chunk = (unit - tile * uint32_t(n_chunks)) * kExactWaves + wid;
+  const uint32_t chunk = (unit - tile * uint32_t(n_chunks)) * per + batch;
   const uint32_t v_local = tile / uint32_t(tpv);
   const uint32_t t = tile - v_local * uint32_t(tpv);
   int tx, ty;
@@ -1721,7 +1775,7 @@ __global__ __launch_bounds__(kWave * kExactWaves) void splat_bwd_exact_kernel(
   wave_lds_sync();
   const float tx0 = float(tx * kTS) + 0.5f, ty0 = float(ty * kTS) + 0.5f;
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  for (uint32_t b = b0 + chunk * kWave; b < e; b += uint32_t(kWave * kExactWaves) * uint32_t(n_chunks)) {
+  for (uint32_t b = b0 + chunk * kWave; b < e; b += kWave * per * uint32_t(n_chunks)) {
     const uint32_t m = min(uint32_t(kWave), e - b);
     uint32_t mask = 0, slot = 0;
     if (uint32_t(lane) < m) {
@@ -2242,9 +2296,12 @@ extern "C" int fgs_project_views_fwd(const fgs_gaussians *g, const fgs_geom *geo
   if (exact) {
     const uint64_t units = L.T * uint64_t(chunks);
     const ExactCam cam = exact_cam(make_geom_dev(geom, opts, view_begin, tg));
-    splat_fwd_exact_kernel<false><<<exact_blocks(units), kWave * kExactWaves, 0, s>>>(
-        at<uint2>(b, L.rng), sv, at<ExactRec>(b, L.rec), tg.tiles_x, tg.tpv, geom->det_w, geom->det_h, uint32_t(L.T),
-        chunks, thr, thr * kCullSlack, cam, part, nullptr);
+    const Share share = exact_share_rule(L.T, chunks, L.K, ws->key_capacity > 0);
+    with_share(share, [&](auto mode) {
+      splat_fwd_exact_kernel<false, decltype(mode)::value><<<exact_blocks(units, share), kWave * kExactWaves, 0, s>>>(
+          at<uint2>(b, L.rng), sv, at<ExactRec>(b, L.rec), at<uint32_t>(b, L.kdev), share.from, tg.tiles_x, tg.tpv,
+          geom->det_w, geom->det_h, uint32_t(L.T), chunks, thr, thr * kCullSlack, cam, part, nullptr);
+    });
     FGS_LAUNCH_CHECK("splat_fwd_exact_kernel");
     if (part_bytes) {
       st = sum_chunks(part, chunks, n_img, img, s);
@@ -2301,9 +2358,12 @@ extern "C" int fgs_project_views_support(const fgs_gaussians *g, const fgs_geom 
   const uint64_t units = L.T * uint64_t(chunks);
   if (use_exact(geom, opts)) {
     const ExactCam cam = exact_cam(make_geom_dev(geom, opts, view_begin, tg));
-    splat_fwd_exact_kernel<true><<<exact_blocks(units), kWave * kExactWaves, 0, s>>>(
-        at<uint2>(b, L.rng), sv, at<ExactRec>(b, L.rec), tg.tiles_x, tg.tpv, geom->det_w, geom->det_h, uint32_t(L.T),
-        chunks, thr, thr * kCullSlack, cam, nullptr, cnt);
+    const Share share = exact_share_rule(L.T, chunks, L.K, ws->key_capacity > 0);
+    with_share(share, [&](auto mode) {
+      splat_fwd_exact_kernel<true, decltype(mode)::value><<<exact_blocks(units, share), kWave * kExactWaves, 0, s>>>(
+          at<uint2>(b, L.rng), sv, at<ExactRec>(b, L.rec), at<uint32_t>(b, L.kdev), share.from, tg.tiles_x, tg.tpv,
+          geom->det_w, geom->det_h, uint32_t(L.T), chunks, thr, thr * kCullSlack, cam, nullptr, cnt);
+    });
     FGS_LAUNCH_CHECK("splat_fwd_exact_kernel<count>");
     return FGS_OK;
   }
@@ -2348,9 +2408,14 @@ extern "C" int fgs_project_views_bwd(const fgs_gaussians *g, const fgs_geom *geo
   if (use_exact(geom, opts)) {
     if (L.K > 0) {
       const int chunks = chunks_per_tile(L.T);
-      splat_bwd_exact_kernel<<<exact_blocks(L.T * uint64_t(chunks)), kWave * kExactWaves, 0, s>>>(
-          at<uint2>(b, L.rng), sv, at<ExactRec>(b, L.rec), tg.tiles_x, tg.tpv, geom->det_w, geom->det_h,
-          uint32_t(L.T), chunks, thr, thr * kCullSlack, exact_cam(G), grad_img, at<float4>(b, L.partials));
+      const Share share = exact_share_rule(L.T, chunks, L.K, ws->key_capacity > 0);
+      with_share(share, [&](auto mode) {
+        splat_bwd_exact_kernel<decltype(mode)::value>
+            <<<exact_blocks(L.T * uint64_t(chunks), share), kWave * kExactWaves, 0, s>>>(
+                at<uint2>(b, L.rng), sv, at<ExactRec>(b, L.rec), at<uint32_t>(b, L.kdev), share.from, tg.tiles_x, tg.tpv,
+                geom->det_w, geom->det_h, uint32_t(L.T), chunks, thr, thr * kCullSlack, exact_cam(G), grad_img,
+                at<float4>(b, L.partials));
+      });
       FGS_LAUNCH_CHECK("splat_bwd_exact_kernel");
     }
     if (ev) FGS_HIP(hipEventRecord(ev[1], s));
