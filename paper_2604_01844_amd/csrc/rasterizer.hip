@@ -479,14 +479,15 @@ struct Share {
   uint64_t from;  // keys from which four waves share a tile; kShareAlways and kShareNever: known on the host
   unsigned blocks;
 };
-// At a fixed key capacity the count is known on the device only: the launch
-// is sized for sharing, and the blocks past the others' end return.
+// At a fixed key capacity the count is known on the device only: where the
+// capacity reaches the line the launch is sized for sharing, and the blocks past
+// the others' end return.
 inline Share share_rule(uint64_t T, uint64_t K, bool capacity) {
   const unsigned one = unsigned((T + 3) / 4);
   if (T >= (1ull << 32) / (4 * kWave)) return {kShareNever, one};  // work-items of a launch
   const uint64_t from = T * (T < 65536 ? T : 65536) / 256;
-  if (capacity) return {from, unsigned(T)};
-  return K >= from ? Share{kShareAlways, unsigned(T)} : Share{kShareNever, one};
+  if (K < from) return {kShareNever, one};
+  return {capacity ? from : kShareAlways, unsigned(T)};
 }
 // The tile of this wave and its first batch; false past the last tile.
 template <int TPB>
@@ -1544,8 +1545,7 @@ enum ShareMode { kOwnTiles, kSharedTiles, kSharedByCount };
 inline Share exact_share_rule(uint64_t T, int chunks, uint64_t K, bool capacity) {
   if (chunks > 1) return {kShareAlways, 0};
   const uint64_t from = T * (T < 65536 ? T : 65536) / 512;
-  if (capacity) return {from, 0};
-  return {K >= from ? kShareAlways : kShareNever, 0};
+  return {K < from ? kShareNever : capacity ? from : kShareAlways, 0};
 }
 
 // Calls f(std::integral_constant<ShareMode, mode>): known to the compiler, since a
