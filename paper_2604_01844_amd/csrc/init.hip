@@ -43,7 +43,7 @@ constexpr int kMaxFilterRow = 8192;
 // owns two 32 x 32 result tiles of one parity. Bound by the matrix cores' FP32
 // rate (64 cycles per instruction, W^2 / 2 products per row: 65 us for 75
 // views of 512^2). Measured there: 2.39 ms with a thread per sample, a
-// division and two LDS reads per tap; 0.136 ms now.
+// division and two LDS reads per tap; 0.130 ms now.
 constexpr int kFilterRows = 32;
 constexpr int kFilterSeg = 512;
 constexpr int kFilterHalf = kFilterSeg / 2;
@@ -187,7 +187,7 @@ constexpr int kPatchWaveRows = kPatchRows / 4;  // rows that each of the four wa
 // locality; from LDS they are two short reads. Bound by VALU issue, about 15
 // instructions per sample. Measured at 75 views of 512^2 and 256^3 voxels:
 // 2.79 ms with a thread per voxel, 1.48 ms with the run but global gathers,
-// 0.89 ms now. A view whose piece is too large for the buffer (a
+// 0.80 ms now. A view whose piece is too large for the buffer (a
 // coarse grid on a fine detector) or that holds voxels at or behind the
 // source is sampled from global memory, with bounds tests.
 template <int RUN>

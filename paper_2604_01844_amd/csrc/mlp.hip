@@ -310,7 +310,7 @@ __device__ __forceinline__ float trilinear_at(const float *__restrict__ vol, con
 // transposed features go through LDS, so that both copies are written in
 // pieces of 64 bytes or more. 50,016 samples: 233 us with a workgroup per
 // sample, whose transposed features were 2-byte stores a row apart and whose
-// corners were loaded one by one behind bounds tests, 90 us now.
+// corners were loaded one by one behind bounds tests, 82 us now.
 constexpr int kGatherRows = 32;
 // Samples of a wave whose loads are in flight together, where their patches lie
 // inside the grid: behind a branch per sample each waited for its own (50,000

@@ -650,11 +650,13 @@ __device__ __forceinline__ void build_quad_lists(uint32_t mask, int lane, uint8_
 // tiles per record, the backward from kSplitBackward. A call that read its pair count back knows; at a fixed key
 // capacity the kernel reads the count on the device, unless the capacity
 // itself is below the line, so both take the same path for the same pairs.
-// Measured: at 17 tiles per record (sigma 7 pixels) the forward gains a fifth
-// and the backward, whose pixels keep three FMAs each, nothing (3.55 ms whole,
-// 3.60 ms split, 75 views of 512^2); at 180 the backward gains a tenth (22.5
-// against 20.0 ms, 4 views of 2048^2); at 6 (sigma 4) a fifth of the quadrants
-// is interior and the second set of lists costs the forward what it saves.
+// Measured, whole and split, 20,000 Gaussians in 75 views of 512^2: forward at 6.6
+// tiles per record 373 and 399 us, 9.6 tiles 546 and 550, 13 tiles 748 and 714, 17
+// tiles 846 and 785, 39 tiles 1,886 and 1,562; backward, whose pixels keep three FMAs
+// each, at 17 tiles 1,240 and 1,329, 27 tiles 1,969 and 1,998, 39 tiles 2,889 and 2,830,
+// 53 tiles 4,012 and 3,863. 50,000 in 4 views of 1024^2: forward at 9.6 tiles 82 and 85, 17
+// tiles 136 and 130; backward at 27 tiles 292 and 295, 53 tiles 572 and 576, 70 tiles 752
+// and 718; in one view of 512^2 the backward crosses at 20.
 constexpr uint64_t kSplitForward = 16, kSplitBackward = 32;
 enum SplitMode { kSplitNever, kSplitAlways, kSplitByCount };
 

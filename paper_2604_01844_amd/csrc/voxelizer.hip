@@ -9,7 +9,7 @@
 //                   half-extents in voxels and the 3D rectangle of 8^3-voxel
 //                   tiles its box touches;
 //   count kernel    a wave per Gaussian with a large rectangle, for four of
-//                   them with small ones: of the rectangle's tiles, those the
+//                   them with small ones (a wave each where they are few): of the rectangle's tiles, those the
 //                   support ellipsoid actually reaches (bounds at the tile's
 //                   centre decide most, the exact box test the rest; about 57%
 //                   of the box's tiles for the standard scan);
@@ -18,7 +18,7 @@
 //   stable radix sort / ranges as in the rasterizer;
 //   forward         one wave per 8^3 tile (grids with few tiles: several, with
 //                   partial volumes); 16 lanes walk a quarter's list, each one
-//                   x-row of 8 voxels; records staged in LDS in batches of 64;
+//                   x-row of 8 voxels (short lists: 64 lanes the tile's); records staged in LDS in batches of 64;
 //                   where Gaussians span many tiles, interior quarters by
 //                   products along the row;
 //   backward        one or four waves per tile; each lane owns one (tile,
@@ -1519,9 +1519,10 @@ uint64_t product_from(const VoxLayout &L) {
 // at once (up to 65,536: 320^3). In grid order the longest lists end last: 200,000
 // Gaussians in the middle of 256^3 0.67 ms, 0.46 longest first and 0.01 for
 // the order; with more tiles the end weighs little and neighbours no longer
-// share an L2 (500,000 of sigma 3 voxels at 512^3, forward and backward 3.57 and
-// 3.75 ms); with short lists the order costs what it gives (3,000 at 256^3
-// 0.41 and 0.42 ms).
+// share an L2 (sigma 3 voxels, 100 keys per tile in a body of 0.7 of the grid's width, grid
+// order and longest first: 64,000 tiles 522 and 519 us, 110,592 tiles 880 and 898,
+// 175,616 tiles 1,333 and 1,429; a narrower body gains up to 110,592 tiles too);
+// with short lists the order costs what it gives (3,000 at 256^3 0.41 and 0.42 ms).
 bool longest_first(const fgs_workspace *ws, const VoxLayout &L) {
   return ws->key_capacity == 0 && L.T <= 65536 && L.K >= kWave * L.T && L.K < product_from(L);
 }
